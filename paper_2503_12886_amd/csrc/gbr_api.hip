@@ -437,7 +437,7 @@ int enqueue_rasterize(gbr_ctx* c, float* images, hipStream_t s) {
   }
   {
     KTimer t(c, GBR_K_COMPOSITE_FWD, s);
-    launch_composite_fwd(a, images, c->chunk, s);
+    launch_composite_fwd(a, images, s);
   }
   launch_classify_tiles(a, true, s);
   GBR_HIP(hipGetLastError());

@@ -6,14 +6,28 @@
 
 namespace gbr {
 
+// Inclusive scan across the wave by DPP adds: four shifts inside the rows of
+// 16 lanes, then the rows' totals carried on (lane 15 of rows 0 and 2 into
+// rows 1 and 3, lane 31 into rows 2 and 3).  Six VALU adds; by lane shuffles
+// each step is an LDS round trip.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_add_u32(uint32_t x) {
+  return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xf, false);
+}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    uint32_t o = __shfl_up(v, d, 64);
-    if (lane >= d) v += o;
-  }
-  return v;
+  v = dpp_add_u32<0x111, 0xf>(v);   // row_shr:1
+  v = dpp_add_u32<0x112, 0xf>(v);
+  v = dpp_add_u32<0x114, 0xf>(v);
+  v = dpp_add_u32<0x118, 0xf>(v);
+  v = dpp_add_u32<0x142, 0xa>(v);   // row_bcast:15
+  return dpp_add_u32<0x143, 0xc>(v);   // row_bcast:31
+}
+
+// Orders the wave's LDS accesses across its lanes (they execute in program
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Exclusive scan of one value per thread across a block of NT threads.

@@ -287,7 +287,7 @@ void launch_tile_scan_classify(const PassArgs& a, uint32_t* block_sums, int64_t 
 // input is ready when the pass starts, run in the bucket scan's launches.
 void launch_depth_order(const PassArgs& a, int64_t max_frame_splats, uint32_t* scan_scratch, const ScanJob& side,
                         hipStream_t s);
-void launch_composite_fwd(const PassArgs& a, float* images, int chunk, hipStream_t s);
+void launch_composite_fwd(const PassArgs& a, float* images, hipStream_t s);
 void launch_composite_bwd(const PassArgs& a, const float* dimages, const float* images, int chunk, hipStream_t s);
 void launch_gather_bwd(const PassArgs& a, const float* raw, float* draw, int64_t max_frame_splats, hipStream_t s);
 void launch_tangent_frames(const float* verts, const int32_t* faces, const float* face_uv, int B, int V, int F,

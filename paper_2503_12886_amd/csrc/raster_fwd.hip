@@ -587,33 +587,32 @@ void launch_tile_lists(const PassArgs& a, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------- compositing
-// One workgroup per tile (pixels to threads: TileMap).
-// CHUNK sorted entries at a time are staged in LDS and read by every thread
-// (broadcast); the tile stops when all its pixels have stopped.
+// (pixels to threads: TileMap)
 template <int T> using TileShape = TileMap<T>;
 
 // Whether a splat's alpha >= 1/255 region may reach the rectangle
 // [x0, x1] x [y0, y1] of pixel centres: the maximum of the concave power
-// ca dx^2 + cb dx dy + cc dy^2 over the rectangle (the mean inside: 0; else
-// the best point of the four edges) against -log2(255) - log2(o), less a margin
-// of 0.01 that keeps the test conservative under float32 rounding (at that
-// margin alpha is 0.7 % below the threshold).  A splat that cannot reach a
-// pixel is never taken there, so skipping it changes nothing.
+// ca dx^2 + cb dx dy + cc dy^2 over the rectangle against
+// -log2(255) - log2(o), less a margin of 0.01 that keeps the test
+// conservative under float32 rounding (at that margin alpha is 0.7 % below
+// the threshold).  The power grows along the way from any point to the mean,
+// so its maximum lies on an edge that faces the mean (or at the mean, when
+// the rectangle holds it): the edge at the rectangle's nearest x and the one
+// at its nearest y are searched, each at its own best point (an error of
+// that point only lowers the value to second order, so an approximate
+// reciprocal will do).  The comparison keeps a NaN.  A splat that cannot
+// reach a pixel is never taken there, so skipping it changes nothing.
 __device__ __forceinline__ bool strip_reach(float4 r0, float4 r1, float x0, float x1, float y0, float y1) {
   const float ca = r0.z, cb = r0.w, cc = r1.x;
   x0 -= r0.x; x1 -= r0.x; y0 -= r0.y; y1 -= r0.y;
-  if (x0 <= 0.0f && x1 >= 0.0f && y0 <= 0.0f && y1 >= 0.0f) return true;
-  const float kx = -cb / (2.0f * cc), ky = -cb / (2.0f * ca);
-  float best = -INFINITY;
-  {
-    const float ya = fminf(fmaxf(kx * x0, y0), y1), yb = fminf(fmaxf(kx * x1, y0), y1);
-    best = fmaxf(best, ca * x0 * x0 + cb * x0 * ya + cc * ya * ya);
-    best = fmaxf(best, ca * x1 * x1 + cb * x1 * yb + cc * yb * yb);
-    const float xa = fminf(fmaxf(ky * y0, x0), x1), xb = fminf(fmaxf(ky * y1, x0), x1);
-    best = fmaxf(best, ca * xa * xa + cb * xa * y0 + cc * y0 * y0);
-    best = fmaxf(best, ca * xb * xb + cb * xb * y1 + cc * y1 * y1);
-  }
-  return best >= -kLog2_255 - r1.y - 0.01f;
+  const float xe = __builtin_amdgcn_fmed3f(0.0f, x0, x1), ye = __builtin_amdgcn_fmed3f(0.0f, y0, y1);
+  const float h = -0.5f * cb;
+  const float ya = __builtin_amdgcn_fmed3f(h * __builtin_amdgcn_rcpf(cc) * xe, y0, y1);
+  const float xb = __builtin_amdgcn_fmed3f(h * __builtin_amdgcn_rcpf(ca) * ye, x0, x1);
+  const float pa = (ca * xe + cb * ya) * xe + cc * ya * ya;
+  const float pb = (ca * xb + cb * ye) * xb + cc * ye * ye;
+  const float thr = -kLog2_255 - r1.y - 0.01f;
+  return !(pa < thr) || !(pb < thr);
 }
 
 // alpha of a splat at a pixel, bit-identical wherever it is evaluated:
@@ -622,59 +621,77 @@ __device__ __forceinline__ bool strip_reach(float4 r0, float4 r1, float x0, floa
 // The clamp is one v_min_f32 (min(power, lo) for every non-NaN power);
 // written as such because fminf would first canonicalise lo, one more
 // instruction per (entry, pixel).
-__device__ __forceinline__ float splat_alpha(float4 r0, float4 r1, float px, float py, float& dx, float& dy,
+__device__ __forceinline__ float splat_alpha(float4 r0, float cc, float lo, float px, float py, float& dx, float& dy,
                                              float& pw_raw) {
 #pragma clang fp contract(off)
   dx = px - r0.x;
   dy = py - r0.y;
-  float pw = __builtin_fmaf(r0.z * dx, dx, r1.y);
+  float pw = __builtin_fmaf(r0.z * dx, dx, lo);
   pw = __builtin_fmaf(r0.w * dx, dy, pw);
-  pw = __builtin_fmaf(r1.x * dy, dy, pw);
+  pw = __builtin_fmaf(cc * dy, dy, pw);
   pw_raw = pw;
   float pc;
-  asm("v_min_f32 %0, %1, %2" : "=v"(pc) : "v"(pw), "v"(r1.y));
+  asm("v_min_f32 %0, %1, %2" : "=v"(pc) : "v"(pw), "v"(lo));
   return __builtin_amdgcn_exp2f(pc);
 }
 
-// A staged candidate: mean, log2-scaled conic, log2 opacity, colour, and the
-// position after it in the tile's list.
+// A staged candidate: mean, log2-scaled conic, log2 opacity, and then what
+// the blending alone reads: colour, and the position after it in the tile's list.
 struct __align__(16) StagedRec {
   float4 r0;    // mx my ca cb
-  float4 r1;    // cc lo r g (lo = log2 opacity)
-  float cb;     // b
-  uint32_t next;  // list position after this entry
+  float2 r1;    // cc lo (lo = log2 opacity)
   float pad[2];
+  float4 c;     // r g b, next (bits): list position after this entry
 };
 
 // One wave per (tile, quadrant): each wave composites its quadrant's pixels
 // on its own, with no barrier shared with the other quadrants of the tile,
-// and stops as soon as its own pixels have stopped.  While a chunk's records
-// are staged, the entries whose alpha >= 1/255 region may reach the wave's
-// pixels are compacted into LDS in list order (a lane tests an entry); the
-// compositing then walks that dense array 4 at a time with a uniform counter.
-// Per (entry, pixel) the front-to-back step is written on the pixel's signed
-// transmittance Te (its transmittance while it runs; once it has stopped,
-// minus the transmittance at the stop), so every decision is a vector
-// compare and select: no per-entry mask logic on the scalar unit.  The tile's list is read
-// in depth order from its bitmap row, a chunk at a time, as the compositing
-// consumes it: a cursor walks the row's segments 64 at a time (their bit
-// counts, prefix-summed across the wave, place each segment in the tile's
-// order), and the words of the segments that overlap the chunk are read a
-// word per lane.  Entries behind the wave's stop are never ordered, mapped
-// to splats or read.  The consumed part of the sorted list is written out
-// for the backward pass (the quadrant waves of a tile write identical
-// values), with a per-quadrant contribution byte per entry and the
-// quadrant's last used position.  The quadrant waves of a tile get block
-// indices of the same residue mod 8, so that they run on one XCD and share
-// its L2.
-template <int T, int CHUNK>
-__global__ __launch_bounds__(64, T == 32 ? 1 : 7) void composite_fwd_kernel(PassArgs a, float* __restrict__ images) {
+// and stops as soon as its own pixels have stopped.
+//
+// The tile's list is a stream of depth ranks, the set bits of its bitmap row
+// in ascending order, produced 64 positions at a time: the row's segments
+// with set bits are found 64 segments at a time from their counts, their
+// words read 64 at a time (a word per lane, the next 64 read ahead), and
+// each word's bits are emitted once, as positions are asked for.  Three
+// batches are in flight: while batch i is composited, the records of batch
+// i + 1 and the splat indices of batch i + 2 are on their way, so that the
+// chain segment counts -> words -> rank -> splat -> record costs its four
+// load latencies once per tile and not once per batch.  That chain bounds a
+// frame rendered alone: the chip holds all its waves at once and the longest
+// tile's serial walk is the pass's time.
+//
+// The entries of a batch whose alpha >= 1/255 region may reach the wave's
+// running pixels are compacted into LDS in list order (a lane tests an
+// entry); the compositing then walks that dense array 4 at a time with a
+// uniform counter.  Per (entry, pixel) the front-to-back step is written on
+// the pixel's signed transmittance Te (its transmittance while it runs; once
+// it has stopped, minus the transmittance at the stop), so every decision is
+// a vector compare and select: no per-entry mask logic on the scalar unit.
+// Entries behind the wave's stop are not composited; at most two batches of
+// them are read.  The consumed part of the sorted list is written out for
+// the backward pass (the quadrant waves of a tile write identical values),
+// with a per-quadrant contribution byte per entry and the quadrant's last
+// used position.  The quadrant waves of a tile get block indices of the same
+// residue mod 8, so that they run on one XCD and share its L2.
+//
+// Measured (us, against a batch read through its four latencies in turn, the
+// words of straddling segments read and emitted twice): one 512 x 512 frame
+// of 50k Gaussians 117 -> 84, 16 of them 223 -> 218 (bound by instruction
+// issue), 10 mesh-bound frames 353 -> 275, 64 uneven frames of 100k 1044 ->
+// 980.  Three entries at a time and 6 waves a SIMD: four at 5 waves gain
+// another 1 % on the longest lists and lose 1 % on full batches, two at 7
+// waves the reverse.  Waves of long lists at a raised issue priority: slower.
+constexpr int kFwdBatch = 64;
+constexpr uint32_t kFwdRing = 256;   // a power of two >= 64 + 32: a whole word fits behind a batch
+
+template <int T>
+__global__ __launch_bounds__(64, T == 32 ? 1 : 6) void composite_fwd_kernel(PassArgs a, float* __restrict__ images) {
   using S = TileShape<T>;
   constexpr int NQ = S::NW;             // quadrants per tile
-  constexpr int U = 4;                  // entries evaluated together (independent alphas)
-  __shared__ StagedRec sr[CHUNK + U];   // the chunk's splat records (one LDS address per entry)
-  __shared__ uint32_t list[CHUNK];      // ranks of the chunk being staged
-  __shared__ uint32_t ovs[64], ovp[64]; // segments of a window that overlap the chunk: id, first position
+  constexpr int U = 3;                  // entries evaluated together (independent alphas)
+  __shared__ StagedRec sr[kFwdBatch + 2 * U];   // the batch's candidates (one LDS address per entry)
+  __shared__ uint32_t list[kFwdRing];       // ranks ahead of the batch, by position mod the ring's size
+  __shared__ uint32_t segs[64];             // the window's segments that have set bits
   if (a.status->overflow) return;
   const int lane = threadIdx.x;
   int r = blockIdx.x, q = 0;
@@ -689,15 +706,14 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 7) void composite_fwd_kernel(Pass
   const FrameDev& F = a.frames[b];
   const int lt = g - F.tile_base;
   const int tx = lt % F.ntx, ty = lt / F.ntx;
-  const uint32_t start = a.tile_start[g], end = a.tile_start[g + 1];
+  const uint32_t start = a.tile_start[g], total = a.tile_start[g + 1] - start;
   const int vt = q * 64 + lane;         // this lane's thread index in the tile's pixel map
   const int lx0 = S::lx0(vt), ly0 = S::ly0(vt);
   // Te: transmittance while the pixel runs; once it has stopped, minus the
   // transmittance at the stop (-0 outside the frame).  last: list position
-  // after the last entry taken; lastk: candidate slot + 1 of the last entry
-  // taken in the current chunk (0: none)
+  // after the last entry taken
   float Te[S::PX], C0[S::PX], C1[S::PX], C2[S::PX], pxf[S::PX], pyf[S::PX];
-  uint32_t last[S::PX], lastk[S::PX];
+  uint32_t last[S::PX];
   bool inside[S::PX];
   bool mine = false;
 #pragma unroll
@@ -707,84 +723,100 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 7) void composite_fwd_kernel(Pass
     pyf[p] = (float)py + 0.5f;
     inside[p] = px < F.W && py < F.H;
     Te[p] = inside[p] ? 1.0f : 0.0f;
-    C0[p] = C1[p] = C2[p] = 0.0f; last[p] = 0; lastk[p] = 0;
+    C0[p] = C1[p] = C2[p] = 0.0f; last[p] = 0;
     mine |= inside[p];
-  }
-  const uint32_t* row = a.tbits + (int64_t)g * a.bitmap_words;
-  const uint16_t* segc = a.seg_cnt + (int64_t)g * a.seg_stride;
-  const int SW = a.seg_words;
-  const uint32_t sh = (uint32_t)__ffs(SW) - 1u;
-  uint32_t vbase = 0, nseg = 0, nv = 0;
-  if (end > start) {
-    vbase = a.bkt_start[b * a.nbk];
-    nv = a.bkt_start[(b + 1) * a.nbk] - vbase;
-    nseg = ((nv + 31) / 32 + SW - 1) / SW;
   }
   // the wave's quadrant origin (pixel centre of its first lane's first pixel);
   // entries are culled against the rectangle of its pixels still running
   static_assert(S::LPR == 8, "the live-rectangle fold assumes 8 lanes per quadrant row");
   const float qx0 = (float)(tx * T + S::qx(vt) * S::QW) + 0.5f;
   const float qy0 = (float)(ty * T + S::qy(vt) * S::QW) + 0.5f;
-  uint32_t wseg = 0, wpos = 0;          // cursor: a segment starting at or before the chunk, its first position
-  bool live = __ballot(mine) != 0ull;
-  for (uint32_t cb = start; live && cb < end; cb += CHUNK) {
-    const int n = (int)min((uint32_t)CHUNK, end - cb);
-    const uint32_t c0 = cb - start, c1 = c0 + (uint32_t)n;
-    // ---- ranks of positions [c0, c1) into list[] ----
-    while (true) {
+  bool live = total > 0 && __ballot(mine) != 0ull;
+
+  // ---- the stream of ranks ----
+  const uint32_t* row = a.tbits + (int64_t)g * a.bitmap_words;
+  const uint16_t* segc = a.seg_cnt + (int64_t)g * a.seg_stride;
+  const uint32_t SW = (uint32_t)a.seg_words, sh = (uint32_t)__ffs(a.seg_words) - 1u;
+  const uint32_t vbase = a.bkt_start[b * a.nbk];
+  const uint32_t nv = a.bkt_start[(b + 1) * a.nbk] - vbase;
+  const uint32_t nseg = ((nv + 31) / 32 + SW - 1) / SW;
+  uint32_t wseg = 0, wcnt = 0;          // next window: its first segment, this lane's segment's count
+  uint32_t nov = 0, kov = 0;            // segments with set bits in the window, and how many were read
+  uint32_t bits = 0, wrank = 0, winc = 0;   // this lane's word: bits not emitted, rank of bit 0, inclusive count
+  uint32_t wtot = 0, wdone = 0;         // (uniform) set bits of the 64 words held, and how many of them are emitted
+  uint32_t bend = 0;                    // (uniform) position after the emitted ones
+  uint32_t nbits = 0, nrank = 0;        // the next 64 words
+  bool nmore = false;                   // (uniform) there are any
+  // issues the load of the next 64 words
+  auto read_words = [&]() {
+    while (kov >= nov && wseg < nseg) {
       const uint32_t sg = wseg + (uint32_t)lane;
-      const uint32_t cnt = segc[min(sg, nseg - 1u)] * (sg < nseg ? 1u : 0u);
-      const uint32_t inc = wave_incl_scan(cnt);
-      const uint32_t p0 = wpos + inc - cnt;          // first position of segment sg
-      const uint32_t wtot = __shfl(inc, 63);
-      const bool ov = cnt != 0u && p0 < c1 && p0 + cnt > c0;
-      const unsigned long long om = __ballot(ov);
-      const int nov = __popcll(om);
-      if (ov) {
-        const uint32_t k = lanes_below(om);
-        ovs[k] = sg;
-        ovp[k] = p0;
-      }
-      __syncthreads();
-      for (int k0 = 0; k0 < nov; k0 += 64 >> sh) {
-        const int k = k0 + (lane >> sh);
-        const int kc = min(k, nov - 1);
-        const uint32_t wi = (uint32_t)lane & (uint32_t)(SW - 1);
-        const uint32_t wq = ovs[kc] * (uint32_t)SW + wi;
-        uint32_t bits = row[wq];
-        if (k >= nov) bits = 0u;
-        const uint32_t c = __popc(bits);
-        uint32_t incw = c;
-        for (int d = 1; d < SW; d <<= 1) {
-          const uint32_t o = __shfl_up(incw, d, SW);
-          if ((int)wi >= d) incw += o;
-        }
-        uint32_t pos = ovp[kc] + incw - c;
-        while (bits) {
-          const uint32_t bit = __ffs(bits) - 1u;
-          bits &= bits - 1u;
-          if (pos >= c0 && pos < c1) list[pos - c0] = wq * 32u + bit;
-          ++pos;
-        }
-      }
-      __syncthreads();
-      const bool more = wpos + wtot < c1 && wseg + 64u < nseg;   // the chunk goes on past this window
-      if (!more) {
-        // next chunk: from the segment holding position c1 (or the next window)
-        const unsigned long long past = __ballot(sg < nseg && p0 + cnt > c1);
-        if (past) {
-          const int j = __ffsll((long long)past) - 1;
-          wpos = __shfl(p0, j);
-          wseg += (uint32_t)j;
-        } else {
-          wseg += 64u;
-          wpos += wtot;
-        }
-        break;
-      }
+      const bool ne = sg < nseg && wcnt != 0u;
+      const unsigned long long om = __ballot(ne);
+      wave_sync();
+      if (ne) segs[lanes_below(om)] = sg;
+      wave_sync();
+      nov = (uint32_t)__popcll(om);
+      kov = 0;
       wseg += 64u;
-      wpos += wtot;
+      wcnt = segc[min(wseg + (uint32_t)lane, nseg - 1u)];
     }
+    const uint32_t k = kov + ((uint32_t)lane >> sh);
+    const bool have = k < nov;
+    const uint32_t wq = have ? segs[k & 63u] * SW + ((uint32_t)lane & (SW - 1u)) : 0u;
+    const uint32_t w = row[wq];
+    nbits = have ? w : 0u;
+    nrank = wq * 32u;
+    nmore = kov < nov;
+    kov += 64u >> sh;
+  };
+  // the splats of positions [c0, c0 + 64) (lanes past the list's end: some splat of the frame)
+  auto read_splats = [&](uint32_t c0) -> uint32_t {
+    if (c0 >= total) return 0u;
+    const uint32_t c1 = min(c0 + (uint32_t)kFwdBatch, total);
+    while (bend < c1) {
+      if (wdone == wtot) {
+        if (!nmore) break;
+        bits = nbits;
+        wrank = nrank;
+        winc = wave_incl_scan(__popc(bits));
+        wtot = (uint32_t)__builtin_amdgcn_readlane((int)winc, 63);
+        wdone = 0;
+        read_words();
+      }
+      // the words that end within the ring (positions from c0 on are in use): all of them, but for dense rows
+      const int space = (int)(c0 + kFwdRing - bend);
+      const unsigned long long fit = __ballot((int)(winc - wdone) <= space);   // lane 0 on; never empty
+      const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)winc, 63 - __clzll((long long)fit));
+      if ((int)(winc - wdone) <= space) {
+        uint32_t at = bend + winc - wdone - __popc(bits);
+        while (bits != 0u) {
+          list[at & (kFwdRing - 1u)] = wrank + (uint32_t)__builtin_ctz(bits);
+          bits &= bits - 1u;
+          ++at;
+        }
+      }
+      bend += upto - wdone;
+      wdone = upto;
+    }
+    wave_sync();
+    const uint32_t rk = list[(c0 + (uint32_t)lane) & (kFwdRing - 1u)];
+    wave_sync();
+    return a.depth_sorted[vbase + min(rk, nv - 1u)];   // (every rank is written)
+  };
+  uint32_t sp0 = 0, sp1 = 0;            // splats of this batch and the next
+  float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;   // this batch's records
+  float qb = 0.f;
+  if (live) {
+    wcnt = segc[min((uint32_t)lane, nseg - 1u)];
+    read_words();
+    sp0 = read_splats(0);
+    const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)sp0 * kRecF);
+    q0 = rec[0]; q1 = rec[1]; qb = rec[2].x;
+    sp1 = read_splats(kFwdBatch);
+  }
+  for (uint32_t c0 = 0; live && c0 < total; c0 += kFwdBatch) {
+    const int n = (int)min((uint32_t)kFwdBatch, total - c0);
     // ---- the rectangle of the pixel centres still running: lanes are 8 per
     // row, so a column runs if any of its 8 lanes does, a row if its byte of
     // the wave mask is nonzero ----
@@ -809,105 +841,96 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 7) void composite_fwd_kernel(Pass
       sy0 = qy0 + (float)(r0l * S::PXW);
       sy1 = qy0 + (float)(r1l * S::PXW + S::PXW - 1);
     }
-    // ---- the chunk's records; the candidates compacted in list order ----
-    constexpr int NB = (CHUNK + 63) / 64;
-    int kslot[NB];                        // this lane's entry of block j: its candidate slot, or -1
-    int ncand = 0;                        // (uniform)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int i = j * 64 + lane;
-      kslot[j] = -1;
-      if (j * 64 >= n) continue;
-      float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;
-      float qb = 0.f;
-      bool c = false;
-      if (i < n) {
-        const uint32_t sp = a.depth_sorted[vbase + min(list[i], nv - 1u)];   // (every rank is written)
-        a.sorted[cb + i] = sp;
-        const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)sp * kRecF);
-        q0 = rec[0]; q1 = rec[1]; qb = rec[2].x;
-        c = live && strip_reach(q0, q1, sx0, sx1, sy0, sy1);
-      }
-      const unsigned long long m = __ballot(c);
-      if (c) {
-        const int k = ncand + (int)lanes_below(m);
-        kslot[j] = k;
-        sr[k].r0 = q0; sr[k].r1 = q1; sr[k].cb = qb; sr[k].next = c0 + (uint32_t)i + 1u;
-      }
-      ncand += __popcll(m);
+    // ---- the batch's candidates compacted in list order ----
+    if (lane < n) a.sorted[start + c0 + lane] = sp0;
+    const bool cand = lane < n && strip_reach(q0, q1, sx0, sx1, sy0, sy1);
+    const unsigned long long cmk = __ballot(cand);
+    const int ncand = __popcll(cmk);      // (uniform)
+    const int kslot = (int)lanes_below(cmk);   // this lane's candidate slot, if its entry is one
+    if (cand) {
+      sr[kslot].r0 = q0;
+      sr[kslot].r1 = make_float2(q1.x, q1.y);
+      sr[kslot].c = make_float4(q1.z, q1.w, qb, __uint_as_float(c0 + (uint32_t)lane + 1u));
     }
-    if (lane < U) {                       // padding entries: opacity 0 (log2 -1e30), never taken; their
-      sr[ncand + lane].r1 = make_float4(0.f, -1e30f, 0.f, 0.f);   // colour 0 (its mean and conic may be
-      sr[ncand + lane].cb = 0.f;                                   // anything: min(power, -1e30) = -1e30)
+    if (lane < U) {                       // padding entries: opacity 0 (log2 -1e30), never taken; their colour 0
+      sr[ncand + lane].r1 = make_float2(0.f, -1e30f);   // (their mean and conic may be anything:
+      sr[ncand + lane].c = make_float4(0.f, 0.f, 0.f, 0.f);   // min(power, -1e30) = -1e30)
     }
-    __syncthreads();
-    // ---- compositing: the candidates in list order, U at a time ----
-    uint32_t took4 = 0u;                  // lane g: bit u = some pixel took candidate 4 g + u
-    for (int k = 0; live && k < ncand; k += U) {
-      float4 r0[U], r1[U];
-      float cb2[U];
+    wave_sync();
+    // ---- the batches behind this one: records of the first, indices of the second ----
+    const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)sp1 * kRecF);
+    q0 = rec[0]; q1 = rec[1]; qb = rec[2].x;
+    sp0 = sp1;
+    sp1 = read_splats(c0 + 2 * kFwdBatch);
+    // ---- compositing: the candidates in list order, U at a time; a group's
+    // conics are read while the group before it is blended, its colours while
+    // its alphas are formed ----
+    unsigned long long tookm = 0ull;      // (uniform) bit 63 - k: some pixel took candidate k
+    float4 r0[U];
+    float2 r1[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) { r0[u] = sr[k + u].r0; r1[u] = sr[k + u].r1; cb2[u] = sr[k + u].cb; }
+    for (int u = 0; u < U; ++u) { r0[u] = sr[u].r0; r1[u] = sr[u].r1; }
+    for (int k = 0; k < ncand; k += U) {
+      float4 col[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) col[u] = sr[k + u].c;
+      float al[S::PX][U];
+#pragma unroll
+      for (int p = 0; p < S::PX; ++p)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          float dx, dy, pwr;
+          al[p][u] = splat_alpha(r0[u], r1[u].x, r1[u].y, pxf[p], pyf[p], dx, dy, pwr);
+        }
+#pragma unroll
+      for (int u = 0; u < U; ++u) { r0[u] = sr[k + U + u].r0; r1[u] = sr[k + U + u].r1; }
+      // (each position is read with its colour: the compiler would sink it
+      // into a branch on the lanes that take the entry)
+#pragma unroll
+      for (int u = 0; u < U; ++u) asm("" : "+v"(col[u].w));
       unsigned long long tm[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) tm[u] = 0ull;
 #pragma unroll
       for (int p = 0; p < S::PX; ++p) {
-        float al[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float dx, dy, pwr;
-          al[u] = splat_alpha(r0[u], r1[u], pxf[p], pyf[p], dx, dy, pwr);
-        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           // the front-to-back step: alpha below 1/255 is skipped (w = 0, Te
           // passes unchanged), T (1 - alpha) < 1e-4 stops the pixel before
           // this entry (Te -> -T); a stopped pixel has Te <= 0, so its tn <= 0
           // stops it again (Te kept: -|Te|) and it takes nothing
-          const float w = (al[u] >= kAlphaMin) ? fminf(al[u], kAlphaMax) : 0.0f;
+          const float w = (al[p][u] >= kAlphaMin) ? fminf(al[p][u], kAlphaMax) : 0.0f;
           const float tn = __builtin_fmaf(-w, Te[p], Te[p]);   // T (1 - alpha), rounded once
           const bool stop = tn < kTMin;
           const float wgt = stop ? 0.0f : w * Te[p];
-          C0[p] = __builtin_fmaf(wgt, r1[u].z, C0[p]);
-          C1[p] = __builtin_fmaf(wgt, r1[u].w, C1[p]);
-          C2[p] = __builtin_fmaf(wgt, cb2[u], C2[p]);
+          C0[p] = __builtin_fmaf(wgt, col[u].x, C0[p]);
+          C1[p] = __builtin_fmaf(wgt, col[u].y, C1[p]);
+          C2[p] = __builtin_fmaf(wgt, col[u].z, C2[p]);
           Te[p] = stop ? -fabsf(Te[p]) : tn;   // one select with source modifiers
           const bool take = wgt > 0.0f;   // w >= 1/255 and Te >= 1e-4: never 0 when taken
-          lastk[p] = take ? (uint32_t)(k + u + 1) : lastk[p];
+          last[p] = take ? __float_as_uint(col[u].w) : last[p];
           tm[u] |= __builtin_amdgcn_ballot_w64(take);
         }
       }
-      // bit u: some pixel took candidate k + u; formed on the scalar unit
-      // (the masks are uniform; the compiler builds it with vector ORs)
+      // bit U - 1 - u: some pixel took candidate k + u; each mask shifted in
+      // on the scalar unit (the compiler builds it with vector ORs)
       uint32_t m4 = 0u;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        uint32_t bit;
-        asm("s_cmp_lg_u64 %1, 0\n\ts_cselect_b32 %0, %2, 0" : "=s"(bit) : "s"(tm[u]), "i"(1 << u) : "scc");
-        m4 |= bit;
-      }
-      took4 = (lane == k / U) ? m4 : took4;
+      for (int u = 0; u < U; ++u)
+        asm("s_cmp_lg_u64 %1, 0\n\ts_addc_u32 %0, %0, %0" : "+s"(m4) : "s"(tm[u]) : "scc");
+      tookm |= ((unsigned long long)m4 << (64 - U)) >> k;   // bit 63 - k: candidate k
       bool mine_now = false;
 #pragma unroll
       for (int p = 0; p < S::PX; ++p) mine_now |= Te[p] > 0.0f;
-      if (__ballot(mine_now) == 0ull) live = false;
+      if (__builtin_amdgcn_ballot_w64(mine_now) == 0ull) {
+        live = false;
+        break;
+      }
     }
-    // the list position after each pixel's last entry taken in this chunk
-#pragma unroll
-    for (int p = 0; p < S::PX; ++p) {
-      if (lastk[p]) last[p] = sr[lastk[p] - 1].next;
-      lastk[p] = 0;
-    }
-    // the quadrant's contribution byte of every entry of the chunk
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int i = j * 64 + lane;
-      const int ks = kslot[j];
-      const uint32_t t4 = (uint32_t)__shfl((int)took4, ks < 0 ? 0 : ks / U);
-      if (i < n) a.cmask[((int64_t)(cb + i) << 2) + q] = (ks >= 0) ? (uint8_t)((t4 >> (ks % U)) & 1u) : (uint8_t)0;
-    }
-    __syncthreads();
+    // the quadrant's contribution byte of every entry of the batch
+    if (lane < n)
+      a.cmask[((int64_t)(start + c0 + lane) << 2) + q] = (uint8_t)(cand ? (tookm >> (63 - kslot)) & 1ull : 0ull);
+    wave_sync();                          // the candidates' slots are rewritten by the next batch
   }
   uint32_t my_last = 0;
 #pragma unroll
@@ -930,20 +953,13 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 7) void composite_fwd_kernel(Pass
   if (lane < 4 && (lane == q || NQ == 1)) a.qlast[g * 4 + lane] = lane == q ? my_last : 0u;
 }
 
-void launch_composite_fwd(const PassArgs& a, float* images, int chunk, hipStream_t s) {
+void launch_composite_fwd(const PassArgs& a, float* images, hipStream_t s) {
   if (a.n_tiles == 0) return;
   const int nq = a.tile == 8 ? 1 : 4;
   const dim3 grid(nq == 1 ? a.n_tiles : div_up(a.n_tiles, 8) * 8 * nq);
-#define GBR_FWD(TT, CC) hipLaunchKernelGGL((composite_fwd_kernel<TT, CC>), grid, dim3(64), 0, s, a, images)
-#define GBR_FWD_T(TT)                      \
-  if (chunk == 64) GBR_FWD(TT, 64);        \
-  else if (chunk == 128) GBR_FWD(TT, 128); \
-  else GBR_FWD(TT, 256);
-  if (a.tile == 8) { GBR_FWD_T(8) }
-  else if (a.tile == 16) { GBR_FWD_T(16) }
-  else { GBR_FWD_T(32) }
-#undef GBR_FWD_T
-#undef GBR_FWD
+  if (a.tile == 8) hipLaunchKernelGGL(composite_fwd_kernel<8>, grid, dim3(64), 0, s, a, images);
+  else if (a.tile == 16) hipLaunchKernelGGL(composite_fwd_kernel<16>, grid, dim3(64), 0, s, a, images);
+  else hipLaunchKernelGGL(composite_fwd_kernel<32>, grid, dim3(64), 0, s, a, images);
 }
 
 // Contributors per pixel, on request: the entries before the pixel's stop
@@ -968,7 +984,7 @@ __global__ __launch_bounds__(256) void count_contrib_kernel(PassArgs a) {
     for (uint32_t i = 0; i < nit; ++i) {
       const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)a.sorted[start + i] * kRecF);
       float dx, dy, pwr;
-      const float al = splat_alpha(rec[0], rec[1], (float)px + 0.5f, (float)py + 0.5f, dx, dy, pwr);
+      const float al = splat_alpha(rec[0], rec[1].x, rec[1].y, (float)px + 0.5f, (float)py + 0.5f, dx, dy, pwr);
       c += al >= kAlphaMin ? 1u : 0u;
     }
     a.n_contrib[pix] = c;
