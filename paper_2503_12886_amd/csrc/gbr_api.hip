@@ -124,7 +124,7 @@ struct gbr_ctx {
   uint32_t* sorted = nullptr;
   uint32_t *order_fwd = nullptr, *order_bwd = nullptr, *cls_cnt = nullptr;
   uint8_t* part_flag = nullptr;
-  uint8_t* cmask = nullptr;
+  unsigned long long* qmask = nullptr;
   // per-frame depth order
   uint32_t *blk_mm = nullptr, *bkt_count = nullptr, *bkt_moff = nullptr, *bkt_start = nullptr;
   unsigned long long *bkeys = nullptr, *bkeys_alt = nullptr;
@@ -214,7 +214,7 @@ PassArgs make_args(gbr_ctx* c) {
   a.tile_count = c->tile_count; a.tile_start = c->tile_start;
   a.tile_last = c->tile_last; a.qlast = c->qlast;
   a.order_fwd = c->order_fwd; a.order_bwd = c->order_bwd; a.cls_cnt = c->cls_cnt;
-  a.tbits = c->tbits; a.sorted = c->sorted; a.part_flag = c->part_flag; a.cmask = c->cmask;
+  a.tbits = c->tbits; a.sorted = c->sorted; a.part_flag = c->part_flag; a.qmask = c->qmask;
   a.nbk = c->nbk;
   a.nblk = c->nblk;
   a.bitmap_words = (int32_t)(((c->max_frame_splats + 31) / 32 + 31) / 32 * 32);
@@ -276,14 +276,14 @@ int check_tiling(int tile, int chunk) {
 
 int alloc_entries(gbr_ctx* c, int64_t cap) {
   ++c->alloc_gen;
-  dfree(c->sorted); dfree(c->part); dfree(c->part_flag); dfree(c->cmask);
+  dfree(c->sorted); dfree(c->part); dfree(c->part_flag); dfree(c->qmask);
   int rc = GBR_OK;
   if ((rc = dalloc(&c->sorted, cap))) return rc;
   if ((rc = dalloc(&c->part_flag, cap + 64))) return rc;   // gather reads 64-entry flag windows
   // every pass leaves the flags zero (the gather resets what it reads), so
   // they are cleared once here
   if (hipMemset(c->part_flag, 0, (size_t)cap + 64) != hipSuccess) return GBR_ERR_HIP;
-  if ((rc = dalloc(&c->cmask, 4 * cap))) return rc;   // a byte per quadrant
+  if ((rc = dalloc(&c->qmask, 4 * qmask_words(cap, c->cap_tiles)))) return rc;
   if ((rc = dalloc(&c->part, cap * kPartF))) return rc;
   c->cap_entries = cap;
   return GBR_OK;
@@ -305,7 +305,7 @@ void free_all(gbr_ctx* c) {
   dfree(c->d_frames); dfree(c->d_status); dfree(c->rec); dfree(c->rect); dfree(c->cnt); dfree(c->soff); dfree(c->dkey);
   dfree(c->tile_count); dfree(c->tile_start); dfree(c->tile_last); dfree(c->qlast); dfree(c->tbits); dfree(c->seg_cnt);
   dfree(c->order_fwd); dfree(c->order_bwd); dfree(c->cls_cnt);
-  dfree(c->sorted); dfree(c->part); dfree(c->part_flag); dfree(c->cmask);
+  dfree(c->sorted); dfree(c->part); dfree(c->part_flag); dfree(c->qmask);
   dfree(c->blk_mm); dfree(c->bkt_count); dfree(c->bkt_moff); dfree(c->bkt_start);
   dfree(c->bkeys); dfree(c->bkeys_alt); dfree(c->depth_sorted); dfree(c->rank);
   dfree(c->n_iter); dfree(c->n_contrib); dfree(c->t_final); dfree(c->scan_scratch); dfree(c->scan_scratch_splat);
@@ -531,7 +531,8 @@ int64_t workspace_bytes(const WorkspaceCaps& k) {
   b += n(2 * loss_partials(3 * k.pixels) + 2) * 4;
   b += n(4 * k.splats + 4096LL * k.frames + 64LL * 64 * 8) * 4;
   b += (int64_t)kBlendMaxFrames * kBlendW64Stride * 8 + 4 * n(k.frames * 1024) * 4;
-  b += n(k.entries) * 4 + n(k.entries + 64) + n(4 * k.entries) + n(k.entries * kPartF) * 4;   // sorted, flags, cmask, part
+  b += n(k.entries) * 4 + n(k.entries + 64) + n(k.entries * kPartF) * 4;   // sorted, flags, part
+  b += n(4 * qmask_words(k.entries, k.tiles)) * 8;
   b += n(k.tbits) * 4 + n(k.seg) * 2;
   if (k.ci_pixels) b += n(3 * k.ci_pixels) * 4 + n(k.ci_splats * kNF) * 4;
   if (k.timing) b += 4 * GBR_K_COUNT * 8;
@@ -1211,18 +1212,21 @@ int gbr_inspect(gbr_ctx* c, int32_t what, void* dst, int64_t* bytes) {
       src = c->n_contrib; n = c->n_pixels * 4; break;
     case 9: {   // one byte per entry, bit w = quadrant w's byte, valid below the quadrant's last position
       if (*bytes < entries) return GBR_ERR_CAPACITY;
-      std::vector<uint32_t> q4((size_t)entries), ts((size_t)c->n_tiles + 1), ql((size_t)c->n_tiles * 4);
-      if (entries > 0) GBR_HIP(hipMemcpy(q4.data(), c->cmask, (size_t)entries * 4, hipMemcpyDeviceToHost));
+      const int64_t words = qmask_words(entries, c->n_tiles);
+      std::vector<unsigned long long> qm((size_t)words * 4);
+      std::vector<uint32_t> ts((size_t)c->n_tiles + 1), ql((size_t)c->n_tiles * 4);
+      GBR_HIP(hipMemcpy(qm.data(), c->qmask, qm.size() * 8, hipMemcpyDeviceToHost));
       GBR_HIP(hipMemcpy(ts.data(), c->tile_start, ts.size() * 4, hipMemcpyDeviceToHost));
       GBR_HIP(hipMemcpy(ql.data(), c->qlast, ql.size() * 4, hipMemcpyDeviceToHost));
       uint8_t* d8 = static_cast<uint8_t*>(dst);
       std::memset(d8, 0, (size_t)entries);
       for (int g = 0; g < c->n_tiles; ++g) {
         for (int64_t i = ts[g]; i < (int64_t)ts[g + 1] && i < entries; ++i) {
-          const uint32_t v = q4[(size_t)i];
+          const int64_t p = i - ts[g];
+          const unsigned long long* word = &qm[4 * (size_t)((ts[g] >> 6) + g + (p >> 6))];
           uint8_t m = 0;
           for (int w = 0; w < 4; ++w)
-            if ((uint32_t)(i - ts[g]) < ql[(size_t)g * 4 + w] && ((v >> (8 * w)) & 1u)) m |= (uint8_t)(1u << w);
+            if (p < (int64_t)ql[(size_t)g * 4 + w] && ((word[w] >> (p & 63)) & 1ull)) m |= (uint8_t)(1u << w);
           d8[i] = m;
         }
       }

@@ -118,7 +118,8 @@ struct PassArgs {
   float* part;              // [E][kPartF] per-entry gradient partials (9 used), by emission slot
   uint8_t* part_flag;       // [E] 1 where the entry's partial is written; zeroed at allocation, set by the
                             // backward compositing, and reset to 0 by the gather that reads it
-  uint8_t* cmask;           // [E][4] byte w = 1: some pixel of quadrant w of the tile took this entry (forward)
+  unsigned long long* qmask;   // [qmask_words][4] bit i of word c: some pixel of the quadrant took entry 64 c + i of
+                            // its tile's list (forward); tile g's words start at (tile_start[g] >> 6) + g
   TangentArgs tg;           // tangent-space binding (tg.on = 0: the pass reads deformed-space Gaussians)
 };
 
@@ -227,6 +228,10 @@ __device__ __forceinline__ void fold16x9(float* x, float* y) {   // x[c] <- x[c]
 #undef GBR_SWAP_PAIR
 
 inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+// Words of the quadrants' masks: a tile's list of n entries takes ceil(n / 64),
+// placed from (tile_start >> 6) + tile on (so that no two tiles share one).
+inline int64_t qmask_words(int64_t entries, int64_t tiles) { return entries / 64 + tiles + 1; }
 
 }  // namespace gbr
 

@@ -2,7 +2,7 @@
 // of the compositing recurrence, per-entry partial gradients reduced across
 // the tile's pixels without atomics, a fixed-order gather per splat, and the
 // adjoint of activation + EWA projection.  Also the photometric loss.
-#include "gbr_internal.h"
+#include "gbr_device.h"
 #include "tangent_ops.h"
 
 namespace gbr {
@@ -38,10 +38,9 @@ __device__ __forceinline__ float splat_alpha_b(float4 r0, float4 r1, float px, f
 // 2 cc) times the first moments, the opacity logit (1 - o) sum t.  Along the
 // traversal each lane keeps only the transmittance and <colour behind,
 // dL/dout>.
-// A wave's sum over its lanes is taken in a fixed order (lane folds, then
-// in-row shifts); the block then adds its waves in order and writes the
-// entry's partial, by emission slot, only if some pixel contributed; a byte
-// flag marks it.
+// A wave's sum over its lanes is taken in a fixed order; the block then adds
+// its waves in order and writes the entry's partial, by emission slot, only
+// if some pixel contributed; a byte flag marks it.
 
 // Folds one entry into a lane's back-to-front state (transmittance in front
 // of the entry, colour behind it) and returns its partial in acc.  Lanes
@@ -110,7 +109,7 @@ __device__ __forceinline__ float rows_transposed9(const float (&v)[9], int lane)
   // partners mirrored inside 8 lanes: the first value in banks 0 and 2, the second in 1 and 3
   asm volatile("s_nop 1\n\t"
                GBR_BANK_PAIR("row_half_mirror", 0, 3, "0x5", "0xa") GBR_BANK_PAIR("row_half_mirror", 1, 4, "0x5", "0xa")
-               "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf"
+               "v_add_f32_dpp %2, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\ts_nop 1"
                : "+v"(a0), "+v"(a2), "+v"(a4)
                : "v"(a1), "v"(a3));
   const bool b1 = lane & 2, b0 = lane & 1;
@@ -128,9 +127,13 @@ __device__ __forceinline__ float row_pair_sum(float x) {
   return x + y;
 }
 
-template <int T, int CHUNK>
-__global__ __launch_bounds__(TileShapeB<T>::NT, T == 16 ? 8 : 1) void composite_bwd_kernel(PassArgs a,
-                                                                         const float* __restrict__ dimages) {
+// Tiles of 32 pixels: four pixels per lane.  The lane's own sums over its
+// pixels come first, so the cross-lane sums are shared by four pixels and
+// stay on the vector unit; CHUNK positions are staged between two barriers.
+template <int CHUNK>
+__global__ __launch_bounds__(TileShapeB<32>::NT) void composite_bwd32_kernel(PassArgs a,
+                                                                             const float* __restrict__ dimages) {
+  constexpr int T = 32;
   static_assert(CHUNK <= 256, "a group's chunk positions are packed one byte each");
   using S = TileShapeB<T>;
   constexpr int U = 4;                      // entries folded per step (independent alphas)
@@ -139,14 +142,13 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, T == 16 ? 8 : 1) void composite_
   __shared__ float4 s2[CHUNK];             // .x only: 16-byte slots share the LDS address of s0 and s1
   __shared__ float red[CHUNK][S::NW][9];
   __shared__ uint32_t wany[CHUNK];         // byte w: wave w wrote red[i][w]
-  __shared__ uint32_t cm[CHUNK];          // byte w: quadrant w took the entry
   __shared__ uint32_t sid[CHUNK];
   if (a.status->overflow) return;
   const int g = tile_of_rank(a.cls_cnt + 33, a.order_bwd, a.n_tiles, blockIdx.x);
   if (g < 0) return;
   const uint32_t L = a.tile_last[g];
   if (L == 0) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t Lw = a.qlast[g * 4 + w];    // this wave's quadrant took nothing at or past Lw
   const int b = frame_of_tile(a.frames, a.B, g);
   const FrameDev& F = a.frames[b];
@@ -175,15 +177,14 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, T == 16 ? 8 : 1) void composite_
     }
   }
   uint8_t* wany8 = reinterpret_cast<uint8_t*>(wany);
-  for (int ce = (int)L; ce > 0; ce -= CHUNK) {
-    const int cbeg = max(0, ce - CHUNK);
-    const int n = ce - cbeg;
+  const unsigned long long* qmask = a.qmask + 4 * ((int64_t)(start >> 6) + g) + w;
+  for (int cbeg = (int)((L - 1) / CHUNK) * CHUNK; cbeg >= 0; cbeg -= CHUNK) {
+    const int n = min(CHUNK, (int)L - cbeg);
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += S::NT) {
       const uint32_t sp = a.sorted[start + cbeg + i];
       const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)sp * kRecF);
       s0[i] = rec[0]; s1[i] = rec[1]; s2[i] = make_float4(rec[2].x, 0.0f, 0.0f, 0.0f);
-      cm[i] = reinterpret_cast<const uint32_t*>(a.cmask)[start + cbeg + i];
       sid[i] = sp;
       wany[i] = 0u;
     }
@@ -194,8 +195,7 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, T == 16 ? 8 : 1) void composite_
     // bits, the same stop position), so every visited entry has a
     // contributing pixel in the wave and its partial is written unchecked.
     for (int gb = (n - 1) & ~63; gb >= 0; gb -= 64) {
-      const int idx = gb + lane;
-      unsigned long long m = __ballot(idx < n && (uint32_t)(cbeg + idx) < Lw && ((cm[idx] >> (8 * w)) & 1u));
+      unsigned long long m = (uint32_t)(cbeg + gb) < Lw ? qmask[4 * (int64_t)((cbeg + gb) >> 6)] : 0ull;
       while (m) {
         int e[U];
         int cnt = 0;
@@ -294,21 +294,310 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, T == 16 ? 8 : 1) void composite_
   }
 }
 
+// One workgroup per tile, a wave per quadrant, one pixel per lane (tiles of 8
+// and 16 pixels).  The list is walked back to front in batches of 64
+// positions (those of the forward pass, whose 64-bit masks say which entries
+// each quadrant took); a wave visits the entries its quadrant took.  A pixel
+// takes an entry here exactly when it took it in the forward pass (the same
+// alpha bits, the same stop position), so every visited entry has a
+// contributing pixel in the wave and its partial is written unchecked.
+//
+// Per visited entry a lane forms two numbers, t and the blending weight; the
+// entry's nine sums over the pixels are their products with quantities that
+// belong to the pixel alone: t with 1, x, y, x^2, xy, y^2 (x, y from the
+// quadrant's centre) and the weight with the pixel's three image gradients.
+// So the sums are taken 8 entries at a time with the roles of the lanes
+// exchanged: the two numbers go to LDS a row of 64 pixels per entry, and lane
+// 8 e + y reads back the 8 pixels of row y of entry e, sums them along x in
+// registers (the powers of x are literals, the image gradients of its 8
+// pixels stay in registers), forms the y moments of its sums, and 20 more
+// operations add the 8 lanes' nine sums: 9 vector operations a visit where
+// nine products and the cross-lane sums of each entry took 27.  The moments
+// about the mean follow from those about the centre once per (tile, entry).
+// (As a product on the matrix cores, 16 v_mfma_f32_16x16x4f32 per 8 entries,
+// the sums cost as much: 6 and 3 of its 16 columns are used, and the vector
+// unit stands still meanwhile.)
+//
+// Records, emission slots and masks of the next batch are read while one is
+// worked on (a batch's chain sorted -> record is two load latencies, and a
+// frame rendered alone is bound by its longest tile's walk).
+// Measured (us, against nine products and lane swaps per entry, the masks as
+// bytes per entry, records read between two barriers): 16 frames of 512 x 512
+// and 50k Gaussians 402 -> 302, 10 mesh-bound ones 638 -> 405, 64 uneven
+// frames of 100k 1285 -> 1080, five of 333 x 500 166 -> 117, one of 128 x 128
+// 88 -> 56.  Bound by instruction issue: 144M vector operations (204M before),
+// 80 % of the slots, 5 waves a SIMD by LDS.
+constexpr int kBwdRow = 68;               // floats per LDS row of 64 pixels: rows 4 banks apart
+
+// One entry folded into a lane's back-to-front state (transmittance in front
+// of the entry, colour behind it), in two parts.  A lane whose pixel did not
+// take the entry folds alpha 0: 1 / (1 - 0) = 1 exactly, so its state passes
+// through unchanged and t and the weight are 0.  (Where rounding makes the
+// clamped quadratic form negative, at a pixel on the mean, the power's
+// gradient passes as it does without the rounding.)
+struct EntryAlpha {
+  float al, inv, cg;     // alpha, 1 / (1 - alpha), <colour, dL/dout>
+  bool below;            // not clamped
+};
+__device__ __forceinline__ EntryAlpha entry_alpha(float a0, bool before_stop, const float4 r1, float cbl, float G0,
+                                                  float G1, float G2) {
+  EntryAlpha x;
+  x.al = before_stop && a0 >= kAlphaMin ? fminf(a0, kAlphaMax) : 0.0f;
+  x.inv = __builtin_amdgcn_rcpf(1.0f - x.al);
+  x.cg = r1.z * G0 + r1.w * G1 + cbl * G2;
+  x.below = a0 < kAlphaMax;                         // min(0.99, .) passes the gradient only below the clamp
+  return x;
+}
+__device__ __forceinline__ void entry_fold(const EntryAlpha& x, float& T_, float& SG, float& t, float& wgt) {
+  const float Ti = T_ * x.inv;                      // transmittance in front of this entry
+  wgt = x.al * Ti;
+  const float dal = Ti * x.cg - SG * x.inv;         // d out / d alpha
+  SG += wgt * x.cg;                                 // <colour behind, dL/dout>
+  T_ = Ti;
+  t = x.below ? x.al * dal : 0.0f;
+}
+
+// The highest set bit of a wave-uniform mask, cleared there (64: none).
+__device__ __forceinline__ uint32_t pop_highest(unsigned long long& m) {
+  int z;
+  asm("s_flbit_i32_b64 %0, %1" : "=s"(z) : "s"(m));   // -1 for 0
+  const uint32_t e = (uint32_t)(63 - z);
+  asm("s_bitset0_b64 %0, %1" : "+s"(m) : "s"(e));     // (64 clears bit 0 of 0)
+  return e;
+}
+
+// The sums over the 8 lanes of each group of 9 values: lane i of a group
+// returns the total of value 4 i0 + 2 i1 + i2 (its bits), and the ninth's in
+// `last`.  Partners by row_half_mirror (whole DPP banks: one bank-masked add
+// in place per value, two wait states before and after for the DPP reads),
+// then 2 and 1 lanes apart.
+#define GBR_BANK_PAIR(x, y)                                                                        \
+  "v_add_f32_dpp %" #x ", %" #x ", %" #x " row_half_mirror row_mask:0xf bank_mask:0x5\n\t"     \
+  "v_add_f32_dpp %" #x ", %" #y ", %" #y " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+__device__ __forceinline__ float octets_transposed9(const float (&v)[9], int lane, float& last) {
+  constexpr int kQuadXor2 = 0x4e, kQuadXor1 = 0xb1;
+  float a0 = v[0], a1 = v[2], a2 = v[4], a3 = v[6], a4 = v[8];
+  asm volatile("s_nop 1\n\t" GBR_BANK_PAIR(0, 5) GBR_BANK_PAIR(1, 6) GBR_BANK_PAIR(2, 7) GBR_BANK_PAIR(3, 8)
+               "v_add_f32_dpp %4, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\ts_nop 1"
+               : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(a4)
+               : "v"(v[1]), "v"(v[3]), "v"(v[5]), "v"(v[7]));
+  const bool b1 = lane & 2, b0 = lane & 1;
+  const float d0 = pair_fold<kQuadXor2>(a0, a1, b1), d1 = pair_fold<kQuadXor2>(a2, a3, b1);
+  a4 += dpp_mov<kQuadXor2, 0xf, 0xf, false>(a4);
+  last = a4 + dpp_mov<kQuadXor1, 0xf, 0xf, false>(a4);
+  return pair_fold<kQuadXor1>(d0, d1, b0);
+}
+#undef GBR_BANK_PAIR
+
+template <int T>
+__global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(PassArgs a,
+                                                                             const float* __restrict__ dimages) {
+  using S = TileShapeB<T>;
+  static_assert(S::PX == 1 && S::QW == 8, "a pixel per lane, quadrants of 8 x 8");
+  constexpr int NW = S::NW;
+  __shared__ float4 st[3][65];              // mx my ca cb | cc lo r g | b; row 64: an entry that is never taken
+  __shared__ uint32_t slot[64];             // emission slot
+  __shared__ float red[65][NW][9];          // a wave's sums of an entry; row 64 takes what a short group leaves over
+  __shared__ __align__(16) float tb[NW][16 * kBwdRow];
+  if (a.status->overflow) return;
+  const int g = tile_of_rank(a.cls_cnt + 33, a.order_bwd, a.n_tiles, blockIdx.x);
+  if (g < 0) return;
+  const uint32_t L = a.tile_last[g];
+  if (L == 0) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = frame_of_tile(a.frames, a.B, g);
+  const FrameDev& F = a.frames[b];
+  const int lt = g - F.tile_base;
+  const int tx = lt % F.ntx, ty = lt / F.ntx;
+  const uint32_t start = a.tile_start[g];
+  const int px = tx * T + S::lx0(threadIdx.x), py = ty * T + S::ly0(threadIdx.x);
+  const float pxf = (float)px + 0.5f, pyf = (float)py + 0.5f;
+  uint32_t nit = 0;
+  float T_ = 1.0f, SG = 0.0f, G0 = 0.0f, G1 = 0.0f, G2 = 0.0f;
+  if (px < F.W && py < F.H) {
+    const float* img_g = dimages + F.pix_base * 3;
+    const int64_t hw = (int64_t)F.W * F.H, pix = (int64_t)py * F.W + px;
+    nit = a.n_iter[F.pix_base + pix];
+    T_ = a.t_final[F.pix_base + pix];
+    G0 = img_g[pix]; G1 = img_g[hw + pix]; G2 = img_g[2 * hw + pix];
+    // <colour behind the current entry, dL/dout>, starts at <T_end * background, dL/dout>
+    SG = T_ * (F.bg[0] * G0 + F.bg[1] * G1 + F.bg[2] * G2);
+  }
+  // the lane's part of the sums: row oy (from the quadrant's centre) of entry
+  // lane / 8 of a group; the image gradients of that row's pixels
+  const float oy = (float)(lane & 7) - 3.5f;
+  float* tw = tb[w];
+  const float* twr = tw + (lane >> 3) * kBwdRow + (lane & 7) * 8;
+  const int value = 4 * (lane & 1) + (lane & 2) + ((lane >> 2) & 1);   // which of the sums the lane ends with
+  float gx[8][3];
+  if (threadIdx.x < 3) st[threadIdx.x][64] = make_float4(0.0f, threadIdx.x == 1 ? -1e30f : 0.0f, 0.0f, 0.0f);
+  {
+    tw[lane] = G0; tw[kBwdRow + lane] = G1; tw[2 * kBwdRow + lane] = G2;
+    wave_sync();
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) gx[k][c] = tw[c * kBwdRow + (lane & 7) * 8 + k];
+    wave_sync();
+  }
+  // this lane's part of a batch's write-out: a quadrant's sums of one entry
+  const int oi = w * (64 / NW) + lane / NW, oq = lane % NW;
+  const float ocx = (float)(tx * T + (oq & 1) * 8) + 4.0f, ocy = (float)(ty * T + (oq >> 1) * 8) + 4.0f;
+  const uint32_t oql = a.qlast[g * 4 + oq];   // quadrant oq took nothing at or past it (its masks end there)
+  const unsigned long long* qmask = a.qmask + 4 * ((int64_t)(start >> 6) + g) + oq;
+  const uint32_t* srt = a.sorted + start;
+
+  // a batch's records and slots, on their way from memory (a lane per entry;
+  // four waves read a piece each: a third of the record, or the slot)
+  float4 p0, p1, p2;
+  uint32_t pslot = 0, sp = 0;
+  auto read_batch = [&](uint32_t s) {
+    const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)s * kRecF);
+    if (NW == 1 || w < 3) p0 = rec[NW == 1 ? 0 : w];
+    if (NW == 1) { p1 = rec[1]; p2 = rec[2]; }
+    if (NW == 1 || w == 3) {   // the splat's offset + row-major index of this tile in its rect
+      const int4 r = a.rect[s];
+      pslot = a.soff[s] + (uint32_t)((ty - r.y) * (r.z - r.x + 1) + (tx - r.x));
+    }
+  };
+  const uint32_t cl = (L - 1u) & ~63u;      // the last batch
+  read_batch(srt[min(cl + (uint32_t)lane, L - 1u)]);   // (lanes past the last used position: its last entry)
+  unsigned long long nmask = qmask[4 * (int64_t)(cl >> 6)];   // quadrant oq's mask of the batch
+  if (cl > 0) sp = srt[cl - 64u + (uint32_t)lane];
+  for (uint32_t c0 = cl;; c0 -= 64u) {
+    // ---- the batch's records to LDS; the next ones on their way ----
+    if (NW == 1 || w < 3) st[NW == 1 ? 0 : w][lane] = p0;
+    if (NW == 1) { st[1][lane] = p1; st[2][lane] = p2; }
+    if (NW == 1 || w == 3) slot[lane] = pslot;
+    const unsigned long long omask = c0 < oql ? nmask : 0ull;
+    unsigned long long m;
+    __syncthreads();
+    if (c0 > 0) {
+      nmask = qmask[4 * (int64_t)((c0 >> 6) - 1u)];
+      read_batch(sp);
+      if (c0 > 64u) sp = srt[c0 - 128u + (uint32_t)lane];
+    }
+    m = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(omask >> 32), w) << 32) |
+        (uint32_t)__builtin_amdgcn_readlane((int)omask, w);   // lane w holds quadrant w's
+    const bool obit = (omask >> oi) & 1ull;
+    bool any = obit;                        // some quadrant took the entry
+    if (NW == 4) {
+      int x = obit ? 1 : 0;
+      x |= __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, false);   // quad_perm: lanes 1 apart, then 2 apart
+      x |= __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, false);
+      any = x != 0;
+    }
+    const float omx = st[0][oi].x - ocx, omy = st[0][oi].y - ocy;
+    const uint32_t oslot = slot[oi];
+    // ---- the quadrant's entries, back to front, in groups of 8 ----
+    while (m) {
+      uint32_t elo = 0x40404040u, ehi = 0x40404040u;   // the group's positions, a byte each (64: no entry)
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {         // a pair of entries
+        if (m) {
+          const uint32_t ea = pop_highest(m), eb = pop_highest(m);   // (eb = 64: none left)
+          const uint32_t pair = ea | (eb << 8);
+          uint32_t& eh = h < 2 ? elo : ehi;
+          eh = (h & 1) ? (eh & 0xffffu) | (pair << 16) : 0x40400000u | pair;
+          const float4 a0 = st[0][ea], a1 = st[1][ea], b0 = st[0][eb], b1 = st[1][eb];
+          const float a2 = st[2][ea].x, b2 = st[2][eb].x;
+          float dx, dy, pwr, ta, wa, tc, wc;
+          const float aa = splat_alpha_b(a0, a1, pxf, pyf, dx, dy, pwr);
+          const float ab = splat_alpha_b(b0, b1, pxf, pyf, dx, dy, pwr);
+          const EntryAlpha xa = entry_alpha(aa, c0 + ea < nit, a1, a2, G0, G1, G2);
+          const EntryAlpha xb = entry_alpha(ab, c0 + eb < nit, b1, b2, G0, G1, G2);
+          entry_fold(xa, T_, SG, ta, wa);
+          entry_fold(xb, T_, SG, tc, wc);
+          tw[(2 * h) * kBwdRow + lane] = ta;
+          tw[(2 * h + 1) * kBwdRow + lane] = tc;
+          tw[(8 + 2 * h) * kBwdRow + lane] = wa;
+          tw[(9 + 2 * h) * kBwdRow + lane] = wc;
+        }
+      }
+      wave_sync();
+      // the row's 8 pixels (a short group's unwritten rows only spoil their own sums)
+      float t[8], wg[8];
+#pragma unroll
+      for (int k = 0; k < 8; k += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(twr + k);
+        const float4 y = *reinterpret_cast<const float4*>(twr + 8 * kBwdRow + k);
+        t[k] = x.x; t[k + 1] = x.y; t[k + 2] = x.z; t[k + 3] = x.w;
+        wg[k] = y.x; wg[k + 1] = y.y; wg[k + 2] = y.z; wg[k + 3] = y.w;
+      }
+      wave_sync();
+      float v[9];
+      {
+        float sm[4], df[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { sm[k] = t[7 - k] + t[k]; df[k] = t[7 - k] - t[k]; }
+        v[5] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
+        v[0] = 3.5f * df[0];
+        v[2] = 12.25f * sm[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+          const float x = 3.5f - (float)k;
+          v[0] = __builtin_fmaf(x, df[k], v[0]);
+          v[2] = __builtin_fmaf(x * x, sm[k], v[2]);
+        }
+        v[1] = oy * v[5];
+        v[3] = oy * v[0];
+        v[4] = oy * v[1];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          v[6 + c] = wg[0] * gx[0][c];
+#pragma unroll
+          for (int k = 1; k < 8; ++k) v[6 + c] = __builtin_fmaf(wg[k], gx[k][c], v[6 + c]);
+        }
+      }
+      float ninth;
+      const float tot = octets_transposed9(v, lane, ninth);
+      const uint32_t e = ((lane & 32 ? ehi : elo) >> (lane & 24)) & 0xffu;
+      red[e][w][value] = tot;
+      if ((lane & 7) == 0) red[e][w][8] = ninth;
+    }
+    __syncthreads();
+    // ---- the batch's partials: the quadrants' sums, moved to the mean, added in order ----
+    if (any) {
+      float v[9];
+#pragma unroll
+      for (int c = 0; c < 9; ++c) v[c] = obit ? red[oi][oq][c] : 0.0f;
+      const float m1x = v[0], m1y = v[1];
+      v[0] = __builtin_fmaf(-omx, v[5], m1x);
+      v[1] = __builtin_fmaf(-omy, v[5], m1y);
+      v[2] = __builtin_fmaf(-omx, v[0], __builtin_fmaf(-omx, m1x, v[2]));
+      v[3] = __builtin_fmaf(-omx, v[1], __builtin_fmaf(-omy, m1x, v[3]));
+      v[4] = __builtin_fmaf(-omy, v[1], __builtin_fmaf(-omy, m1y, v[4]));
+      if (NW == 4) {                        // (an entry's four lanes take this branch together)
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+          v[c] += dpp_mov<0xb1, 0xf, 0xf, false>(v[c]);
+          v[c] += dpp_mov<0x4e, 0xf, 0xf, false>(v[c]);
+        }
+      }
+      float4* dst = reinterpret_cast<float4*>(a.part + (int64_t)oslot * kPartF);
+      if (NW == 1 || oq == 0) dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+      if (NW == 1 || oq == 1) dst[1] = make_float4(v[4], v[5], v[6], v[7]);
+      if (NW == 1 || oq == 2) dst[2] = make_float4(v[8], 0.0f, 0.0f, 0.0f);
+      if (NW == 1 || oq == 3) a.part_flag[oslot] = 1;
+    }
+    if (c0 == 0) break;
+  }
+}
+
 void launch_composite_bwd(const PassArgs& a, const float* dimages, const float* images, int chunk, hipStream_t s) {
   (void)images;
   if (a.n_tiles == 0) return;
   const dim3 grid(a.n_tiles);
-#define GBR_BWD(TT, CC) \
-  hipLaunchKernelGGL((composite_bwd_kernel<TT, CC>), grid, dim3(TileShapeB<TT>::NT), 0, s, a, dimages)
-#define GBR_BWD_T(TT)                      \
-  if (chunk == 64) GBR_BWD(TT, 64);        \
-  else if (chunk == 128) GBR_BWD(TT, 128); \
-  else GBR_BWD(TT, 256);
-  if (a.tile == 8) { GBR_BWD_T(8) }
-  else if (a.tile == 16) { GBR_BWD_T(16) }
-  else { GBR_BWD_T(32) }
-#undef GBR_BWD_T
-#undef GBR_BWD
+  if (a.tile == 8) {
+    hipLaunchKernelGGL(composite_bwd_kernel<8>, grid, dim3(TileShapeB<8>::NT), 0, s, a, dimages);
+  } else if (a.tile == 16) {
+    hipLaunchKernelGGL(composite_bwd_kernel<16>, grid, dim3(TileShapeB<16>::NT), 0, s, a, dimages);
+  } else {
+    const dim3 nt(TileShapeB<32>::NT);
+    if (chunk == 64) hipLaunchKernelGGL(composite_bwd32_kernel<64>, grid, nt, 0, s, a, dimages);
+    else if (chunk == 128) hipLaunchKernelGGL(composite_bwd32_kernel<128>, grid, nt, 0, s, a, dimages);
+    else hipLaunchKernelGGL(composite_bwd32_kernel<256>, grid, nt, 0, s, a, dimages);
+  }
 }
 
 // ---------------------------------------------------------------- gather + projection adjoint

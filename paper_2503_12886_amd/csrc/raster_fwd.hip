@@ -670,8 +670,8 @@ struct __align__(16) StagedRec {
 // Entries behind the wave's stop are not composited; at most two batches of
 // them are read.  The consumed part of the sorted list is written out for
 // the backward pass (the quadrant waves of a tile write identical values),
-// with a per-quadrant contribution byte per entry and the quadrant's last
-// used position.  The quadrant waves of a tile get block indices of the same
+// with a 64-bit mask per batch of the entries that the quadrant took and the
+// quadrant's last used position.  The quadrant waves of a tile get block indices of the same
 // residue mod 8, so that they run on one XCD and share its L2.
 //
 // Measured (us, against a batch read through its four latencies in turn, the
@@ -927,9 +927,9 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 6) void composite_fwd_kernel(Pass
         break;
       }
     }
-    // the quadrant's contribution byte of every entry of the batch
-    if (lane < n)
-      a.cmask[((int64_t)(start + c0 + lane) << 2) + q] = (uint8_t)(cand ? (tookm >> (63 - kslot)) & 1ull : 0ull);
+    // the entries of the batch that the quadrant took
+    const unsigned long long taken = __ballot(cand && ((tookm >> (63 - kslot)) & 1ull));
+    if (lane == 0) a.qmask[4 * ((int64_t)(start >> 6) + g + (c0 >> 6)) + q] = taken;
     wave_sync();                          // the candidates' slots are rewritten by the next batch
   }
   uint32_t my_last = 0;
