@@ -7,65 +7,140 @@ namespace gbr {
 
 // ---------------------------------------------------------------- MLP forward
 // One workgroup per frame runs the three layers back to back: the layer's
-// input vector sits in LDS, each wave forms output units four at a time
-// (lanes over the input, weight rows read coalesced, then a fixed-order sum
-// across the wave).  Pre-activations are kept (z1, z2 for the backward; the
-// ReLU of a layer is applied when the next layer reads them).
+// input vector sits in LDS, each wave forms 16 output units at a time (4 of
+// the short last layer), lanes over the input.  Weight rows are read
+// coalesced at a uniform row address and one lane offset, so the loads cost no
+// vector arithmetic, and the units' sums over the wave are taken together:
+// each halving step of the butterfly (partners 32, 16, 8, 4, 2, 1 apart, the
+// same pairs as one butterfly per unit) folds two units' registers into one,
+// 32 operations for 16 units where 16 separate butterflies take 96 lane
+// exchanges.  When the weights of all three layers fit the registers (inputs
+// up to 64, hidden layers up to 256) every load is issued before the first
+// product, so that one load latency precedes the layers instead of three.
+// Bound by latency and one CU's issue: a frame's workgroup 14.3 -> 6.9 us
+// at 56-256-256-20 (2000 -> 400 vector operations a wave).  Pre-activations
+// are kept (z1, z2 for the backward; the ReLU of a layer is applied when the
+// next layer reads them).
 constexpr int kMlpThreads = 1024;
 constexpr int kMlpWaves = kMlpThreads / 64;
 constexpr int kMlpMaxIn = 1024;
+constexpr int kMlpRows = 16, kMlpRowsOut = 4;   // units a wave forms together: hidden layers, last layer
 
-__device__ __forceinline__ float wave_sum_f32(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// x <- the two registers' sums over partners 32 (16) lanes apart: x's in the
+// lower half (even rows), y's in the upper (odd rows).
+__device__ __forceinline__ float fold32(float x, float y) {
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(x), "+v"(y));
+  return x + y;
+}
+__device__ __forceinline__ float fold16(float x, float y) {
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(x), "+v"(y));
+  return x + y;
+}
+// The same 8 (4) lanes apart inside the rows of 16: bank-masked DPP adds in
+// place, with the two wait states that DPP reads need before and after.
+__device__ __forceinline__ float fold8(float x, float y) {
+  asm volatile("s_nop 1\n\t"
+               "v_add_f32_dpp %0, %0, %0 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+               "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc\n\ts_nop 1"
+               : "+v"(x) : "v"(y));
+  return x;
+}
+__device__ __forceinline__ float fold4(float x, float y) {
+  asm volatile("s_nop 1\n\t"
+               "v_add_f32_dpp %0, %0, %0 row_shl:4 row_mask:0xf bank_mask:0x5\n\t"
+               "v_add_f32_dpp %0, %1, %1 row_shr:4 row_mask:0xf bank_mask:0xa\n\ts_nop 1"
+               : "+v"(x) : "v"(y));
+  return x;
 }
 
-// out[j] = bias[j] + sum_c W[j][c] act(in[c]) for j < n_out; act = ReLU when relu_in.
-// A wave forms kRows output units at a time over passes of 256 inputs: lane
-// l takes inputs c0 + l + 64 t (t < 4), and every weight load of a pass
-// (rows and inputs clamped into range, masked afterwards) is issued before
-// the first product, so a layer costs a load latency per pass rather than
-// one per input step.
-constexpr int kRows = 8;
+// The sums over the wave of R values a lane: lane l returns value l R / 64's.
+__device__ __forceinline__ float wave_sums(float (&s)[16]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) s[i] = fold32(s[i], s[i + 8]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s[i] = fold16(s[i], s[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) s[i] = fold8(s[i], s[i + 2]);
+  float x = fold4(s[0], s[1]);
+  x += dpp_mov<0x4e, 0xf, 0xf, false>(x);
+  return x + dpp_mov<0xb1, 0xf, 0xf, false>(x);
+}
+__device__ __forceinline__ float wave_sums(float (&s)[4]) {
+  float x = fold16(fold32(s[0], s[2]), fold32(s[1], s[3]));
+  x += dpp_mov<0x128, 0xf, 0xf, false>(x);   // row_ror:8
+  x += dpp_mov<0x124, 0xf, 0xf, false>(x);   // row_ror:4 (the row has period 8 by now)
+  x += dpp_mov<0x4e, 0xf, 0xf, false>(x);
+  return x + dpp_mov<0xb1, 0xf, 0xf, false>(x);
+}
 
-__device__ __forceinline__ void mlp_layer(const float* __restrict__ W, const float* __restrict__ bias,
-                                          const float* in, int n_in, int n_out, bool relu_in,
-                                          float* __restrict__ out_g, float* out_l) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int j0 = w * kRows; j0 < n_out; j0 += kMlpWaves * kRows) {
-    float s[kRows];
+// Weights of units [j0, j0 + R) at inputs c0 + lane + 64 t, t < T4 (units and
+// inputs clamped into range; the inputs' values are zeroed past n_in).  j0 is
+// wave-uniform.
+template <int R, int T4>
+__device__ __forceinline__ void mlp_weights(const float* __restrict__ W, int n_in, int n_out, int j0, int c0,
+                                            float (&wv)[R][T4]) {
+  const int lane = threadIdx.x & 63;
+  uint32_t c[T4];                          // byte offsets (32 bits: the loads take them beside a scalar row address)
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) s[r] = 0.0f;
-    for (int c0 = 0; c0 < n_in; c0 += 256) {
-      float xv[4], wv[kRows][4];
+  for (int t = 0; t < T4; ++t) c[t] = 4u * (uint32_t)min(c0 + 64 * t + lane, n_in - 1);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int c = c0 + 64 * t + lane;
-        const int cc = min(c, n_in - 1);
+  for (int r = 0; r < R; ++r) {
+    const char* row = reinterpret_cast<const char*>(W + (int64_t)min(j0 + r, n_out - 1) * n_in);
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) wv[r][t] = W[(int64_t)min(j0 + r, n_out - 1) * n_in + cc];
-        const float v = in[cc];
-        xv[t] = c < n_in ? (relu_in ? fmaxf(v, 0.0f) : v) : 0.0f;
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) s[r] = __builtin_fmaf(wv[r][t], xv[t], s[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) s[r] = wave_sum_f32(s[r]);
-    if (lane < kRows && j0 + lane < n_out) {
-      float v = s[0];
-#pragma unroll
-      for (int r = 1; r < kRows; ++r) v = lane == r ? s[r] : v;
-      v += bias[j0 + lane];
-      out_g[j0 + lane] = v;
-      if (out_l) out_l[j0 + lane] = v;
-    }
+    for (int t = 0; t < T4; ++t) wv[r][t] = *reinterpret_cast<const float*>(row + c[t]);
   }
 }
 
+template <int R, int T4>
+__device__ __forceinline__ void mlp_products(const float (&wv)[R][T4], const float* in, int n_in, int c0, bool relu_in,
+                                             float (&s)[R]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int t = 0; t < T4; ++t) {
+    const int c = c0 + 64 * t + lane;
+    const float v = in[min(c, n_in - 1)];
+    const float x = c < n_in ? (relu_in ? fmaxf(v, 0.0f) : v) : 0.0f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = __builtin_fmaf(wv[r][t], x, s[r]);
+  }
+}
+
+// out[j0 + i] = bias + the sums, i < R
+template <int R>
+__device__ __forceinline__ void mlp_store(float (&s)[R], const float* __restrict__ bias, int n_out, int j0,
+                                          float* __restrict__ out_g, float* out_l) {
+  const int lane = threadIdx.x & 63;
+  const float tot = wave_sums(s);
+  const int j = j0 + lane * R / 64;
+  if (lane % (64 / R) == 0 && j < n_out) {
+    const float v = tot + bias[j];
+    out_g[j] = v;
+    if (out_l) out_l[j] = v;
+  }
+}
+
+// out[j] = bias[j] + sum_c W[j][c] act(in[c]) for j < n_out; act = ReLU when relu_in.
+template <int R>
+__device__ __forceinline__ void mlp_layer(const float* __restrict__ W, const float* __restrict__ bias,
+                                          const float* in, int n_in, int n_out, bool relu_in,
+                                          float* __restrict__ out_g, float* out_l) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int j0 = w * R; j0 < n_out; j0 += kMlpWaves * R) {
+    float s[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = 0.0f;
+    for (int c0 = 0; c0 < n_in; c0 += 256) {
+      float wv[R][4];
+      mlp_weights(W, n_in, n_out, j0, c0, wv);
+      mlp_products(wv, in, n_in, c0, relu_in, s);
+    }
+    mlp_store(s, bias, n_out, j0, out_g, out_l);
+  }
+}
+
+// HELD: inputs up to 64 and hidden layers up to 256 (a block of rows per
+// wave): the three layers' weights are read at once.
+template <bool HELD>
 __global__ __launch_bounds__(kMlpThreads) void mlp_fwd_kernel(const float* __restrict__ params,
                                                               const float* __restrict__ theta, int d_in, int hidden,
                                                               int K, float* __restrict__ psi, float* __restrict__ z1,
@@ -78,19 +153,57 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_fwd_kernel(const float* __res
   const float* b2 = W2 + (int64_t)hidden * hidden;
   const float* W3 = b2 + hidden;
   const float* b3 = W3 + (int64_t)K * hidden;
-  for (int t = threadIdx.x; t < d_in; t += kMlpThreads) xa[t] = theta[(int64_t)b * d_in + t];
-  __syncthreads();
-  mlp_layer(W1, b1, xa, d_in, hidden, false, z1 + (int64_t)b * hidden, xb);
-  __syncthreads();
-  mlp_layer(W2, b2, xb, hidden, hidden, true, z2 + (int64_t)b * hidden, xa);
-  __syncthreads();
-  mlp_layer(W3, b3, xa, hidden, K, true, psi + (int64_t)b * K, nullptr);
+  z1 += (int64_t)b * hidden;
+  z2 += (int64_t)b * hidden;
+  psi += (int64_t)b * K;
+  if constexpr (HELD) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j0 = w * kMlpRows, k0 = w * kMlpRowsOut;
+    const float th = (int)threadIdx.x < d_in ? theta[(int64_t)b * d_in + threadIdx.x] : 0.0f;
+    float w1[kMlpRows][1], w2[kMlpRows][4], w3[kMlpRowsOut][4];
+    mlp_weights(W1, d_in, hidden, j0, 0, w1);
+    mlp_weights(W2, hidden, hidden, j0, 0, w2);
+    mlp_weights(W3, hidden, K, k0, 0, w3);
+    __builtin_amdgcn_sched_barrier(0);      // every load before the layers
+    if ((int)threadIdx.x < d_in) xa[threadIdx.x] = th;
+    __syncthreads();
+    float s[kMlpRows], so[kMlpRowsOut];
+#pragma unroll
+    for (int r = 0; r < kMlpRows; ++r) s[r] = 0.0f;
+    mlp_products(w1, xa, d_in, 0, false, s);
+    mlp_store(s, b1, hidden, j0, z1, xb);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kMlpRows; ++r) s[r] = 0.0f;
+    mlp_products(w2, xb, hidden, 0, true, s);
+    mlp_store(s, b2, hidden, j0, z2, xa);
+    __syncthreads();
+    if (k0 < K) {
+#pragma unroll
+      for (int r = 0; r < kMlpRowsOut; ++r) so[r] = 0.0f;
+      mlp_products(w3, xa, hidden, 0, true, so);
+      mlp_store(so, b3, K, k0, psi, nullptr);
+    }
+  } else {
+    for (int t = threadIdx.x; t < d_in; t += kMlpThreads) xa[t] = theta[(int64_t)b * d_in + t];
+    __syncthreads();
+    mlp_layer<kMlpRows>(W1, b1, xa, d_in, hidden, false, z1, xb);
+    __syncthreads();
+    mlp_layer<kMlpRows>(W2, b2, xb, hidden, hidden, true, z2, xa);
+    __syncthreads();
+    mlp_layer<kMlpRowsOut>(W3, b3, xa, hidden, K, true, psi, nullptr);
+  }
 }
 
 void launch_mlp_fwd(const float* params, const float* theta, int B, int d_in, int hidden, int K, float* psi,
                     float* z1, float* z2, hipStream_t s) {
   if (B == 0) return;
-  hipLaunchKernelGGL(mlp_fwd_kernel, dim3(B), dim3(kMlpThreads), 0, s, params, theta, d_in, hidden, K, psi, z1, z2);
+  if (d_in <= 64 && hidden <= kMlpWaves * kMlpRows && K <= kMlpWaves * kMlpRowsOut)
+    hipLaunchKernelGGL(mlp_fwd_kernel<true>, dim3(B), dim3(kMlpThreads), 0, s, params, theta, d_in, hidden, K, psi, z1,
+                       z2);
+  else
+    hipLaunchKernelGGL(mlp_fwd_kernel<false>, dim3(B), dim3(kMlpThreads), 0, s, params, theta, d_in, hidden, K, psi,
+                       z1, z2);
 }
 
 // ---------------------------------------------------------------- MLP backward
