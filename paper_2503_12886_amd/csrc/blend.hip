@@ -16,6 +16,8 @@
 // batch it is blended in.  dweights contracts over N*16 elements into a
 // B x K result: a long dense contraction, done on the matrix cores
 // (v_mfma_f32_16x16x4f32) with per-wave partials reduced in a fixed order.
+#include <type_traits>
+
 #include "gbr_internal.h"
 
 namespace gbr {
@@ -24,6 +26,25 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlendThreads = 256;
 constexpr int kFrameGroup = 16;        // frames whose weights are staged together
+
+// Kernels that keep a value per slice in registers are instantiated for every
+// multiple of 8 slices and launched at the smallest that holds K + 1: slices
+// past K are read (clamped) and multiplied for nothing: of 100k Gaussians and
+// 8 frames the blend of 41 slices took 74 us in a 64-slice kernel and takes 62
+// in one of 48, 31 slices 69 -> 45 (of 32), 6 slices 26 -> 19 (of 8).
+template <typename F>
+static void with_slices(int K, F&& launch) {
+  switch (K / 8) {                     // ceil((K + 1) / 8) = K / 8 + 1
+    case 0: launch(std::integral_constant<int, 8>()); break;
+    case 1: launch(std::integral_constant<int, 16>()); break;
+    case 2: launch(std::integral_constant<int, 24>()); break;
+    case 3: launch(std::integral_constant<int, 32>()); break;
+    case 4: launch(std::integral_constant<int, 40>()); break;
+    case 5: launch(std::integral_constant<int, 48>()); break;
+    case 6: launch(std::integral_constant<int, 56>()); break;
+    default: launch(std::integral_constant<int, 64>()); break;
+  }
+}
 
 // ---------------------------------------------------------------- forward
 // The frames' weights, as float64 with the implicit 1 of slice 0, are laid
@@ -64,10 +85,9 @@ void launch_blend_fwd(const float* bases, const float* weights, int B, int K, in
   if (N == 0 || B == 0) return;
   hipLaunchKernelGGL(blend_weights_f64_kernel, dim3(B), dim3(kBlendW64Stride), 0, s, weights, K, w64);
   const dim3 grid(div_up(N * kNF, kBlendThreads));
-  if (K + 1 <= 24)
-    hipLaunchKernelGGL(blend_fwd_kernel<24>, grid, dim3(kBlendThreads), 0, s, bases, w64, B, K, N, raw);
-  else
-    hipLaunchKernelGGL(blend_fwd_kernel<64>, grid, dim3(kBlendThreads), 0, s, bases, w64, B, K, N, raw);
+  with_slices(K, [&](auto km) {
+    hipLaunchKernelGGL(blend_fwd_kernel<km()>, grid, dim3(kBlendThreads), 0, s, bases, w64, B, K, N, raw);
+  });
 }
 
 // ---------------------------------------------------------------- adjoint: dbases
@@ -173,12 +193,12 @@ void launch_blend_adam(const float* draw, const float* weights, int B, int K, in
   launch_adam_tick(status, group, b1, b2, s);
   if (N == 0 || B == 0) return;
   const dim3 g1(div_up(N * kNF, kBlendThreads));
-  if (K + 1 <= 24)
-    hipLaunchKernelGGL(blend_adam_kernel<24>, g1, dim3(kBlendThreads), 0, s, draw, weights, B, K, N, p, m, v, status,
+  // (past 32 slices one of 64: the sizes between take more registers, 119 to
+  // 153 against 109, and at 100k x 40 the update 396 us against 347)
+  with_slices(K < 32 ? K : kBlendW64Stride - 1, [&](auto km) {
+    hipLaunchKernelGGL(blend_adam_kernel<km()>, g1, dim3(kBlendThreads), 0, s, draw, weights, B, K, N, p, m, v, status,
                        group, lr, b1, b2, eps);
-  else
-    hipLaunchKernelGGL(blend_adam_kernel<64>, g1, dim3(kBlendThreads), 0, s, draw, weights, B, K, N, p, m, v, status,
-                       group, lr, b1, b2, eps);
+  });
 }
 
 // ---------------------------------------------------------------- adjoint: dweights
@@ -323,12 +343,11 @@ void launch_blend_bwd(const float* draw, const float* bases, const float* weight
                       hipStream_t s) {
   if (N == 0 || B == 0) return;
   const dim3 g1(div_up(N * kNF, kBlendThreads));
-  if (dbases && K + 1 <= 24)
-    hipLaunchKernelGGL(blend_dbases_kernel<24>, g1, dim3(kBlendThreads), 0, s, draw, weights, B, K, N, dbases,
-                       accumulate);
-  else if (dbases)
-    hipLaunchKernelGGL(blend_dbases_kernel<64>, g1, dim3(kBlendThreads), 0, s, draw, weights, B, K, N, dbases,
-                       accumulate);
+  if (dbases)
+    with_slices(K, [&](auto km) {
+      hipLaunchKernelGGL(blend_dbases_kernel<km()>, g1, dim3(kBlendThreads), 0, s, draw, weights, B, K, N, dbases,
+                         accumulate);
+    });
   if (K == 0) return;
   const dim3 g2(div_up(N * kNF, 4 * kDwSpan));
   const bool small = B <= 16 && K <= 32;
