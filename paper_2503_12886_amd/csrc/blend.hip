@@ -16,6 +16,7 @@
 // batch it is blended in.  dweights contracts over N*16 elements into a
 // B x K result: a long dense contraction, done on the matrix cores
 // (v_mfma_f32_16x16x4f32) with per-wave partials reduced in a fixed order.
+#include <algorithm>
 #include <type_traits>
 
 #include "gbr_internal.h"
@@ -202,128 +203,143 @@ void launch_blend_adam(const float* draw, const float* weights, int B, int K, in
 }
 
 // ---------------------------------------------------------------- adjoint: dweights
-// Wave w covers the flattened elements [w * kDwSpan, (w + 1) * kDwSpan) of
-// the N*16 per-slice vectors in blocks of 16: lane (x, q) loads 4 consecutive
-// elements (q-th quarter) of frame x's draw and of slice x's (and 16 + x's)
-// base; each of the 4 components feeds one 16x16x4 product (frames x slices,
-// contracted over the 4 quarters).  The pad features (14, 15) are skipped.
-// Writes a [B][K] partial per wave, or per workgroup for small tiles (B <= 16,
-// K <= 32: the four waves are added in LDS first, a quarter of the partials).
+// A wave covers the flattened elements of a span of the N*16 per-slice
+// vectors in blocks of 16: lane (x, q) loads 4 consecutive elements (q-th
+// quarter) of frame x's draw and of slice x's (and 16 + x's, ...) base; each
+// of the 4 components feeds one 16x16x4 product per 16 frames and 16 slices,
+// contracted over the 4 quarters.  The pad features (14, 15) are skipped.
+// The workgroup's four waves are added in LDS and it writes one [B][K]
+// partial.  At most kDwBlocks workgroups run, each wave over several spans
+// whose sums are added in span order, and the kernel is instantiated per 16
+// frames and 16 slices: bound by reading draw and the bases once.  64 frames
+// of 100k Gaussians x 20: 172 + 62 (reduction) -> 150 + 5 us, where a partial per
+// wave of 256 elements (32 MB, re-read at a stride of a partial) and products
+// of 64 x 64 for 64 x 20 had cost as much again as the reading.  (The line for
+// several spans: with twice the workgroups it takes 158 + 8, with as many
+// spans for every wave 172.)
 constexpr int kDwSpan = 256;
+constexpr int kDwBlocks = 1024;
 
-template <int MAXBT, int MAXKT>
+template <int BT, int KT, bool MULTI>   // MULTI: several spans per wave
 __global__ __launch_bounds__(256) void blend_dweights_kernel(const float* __restrict__ draw,
                                                               const float* __restrict__ bases, int B, int K,
                                                               int64_t N, float* __restrict__ partials) {
-  const int lane = threadIdx.x & 63;
+  __shared__ float ws[4][256];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int x = lane & 15, q = lane >> 4;
-  const int64_t gw = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int64_t L = N * kNF;
-  const int64_t e_begin = gw * kDwSpan;
-  const int64_t e_end = min(L, e_begin + kDwSpan);
-  const int nbt = (B + 15) / 16, nkt = (K + 15) / 16;
-  f4 acc[MAXBT][MAXKT];
-#pragma unroll
-  for (int i = 0; i < MAXBT; ++i)
-#pragma unroll
-    for (int j = 0; j < MAXKT; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  const int64_t spans = (L + kDwSpan - 1) / kDwSpan;
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
+  f4 acc[BT][KT], sum[BT][KT];              // a span's products; the spans before it
+#pragma unroll
+  for (int i = 0; i < BT; ++i)
+#pragma unroll
+    for (int j = 0; j < KT; ++j) acc[i][j] = sum[i][j] = zero;
   // Blocks of 16 elements, G at a time: every load of a group is issued
-  // before its products, and the products of out-of-range tiles are taken on
+  // before its products, and the products of out-of-range rows are taken on
   // zeros rather than branched around, so that the group's loads are in
-  // flight together.  A wave's last group may run past its blocks: those
-  // re-read the wave's last block and are zeroed.  The products are summed
-  // block by block as without grouping.
-  constexpr int G = (MAXBT + MAXKT <= 4) ? 4 : 1;
-  const int nit = e_end > e_begin ? (int)((e_end - e_begin) / 16) : 0;   // (uniform; L is a multiple of 16)
-  for (int it0 = 0; it0 < nit; it0 += G) {
-    f4 a[G][MAXBT], bb[G][MAXKT];
+  // flight together.  A span's last group may run past its blocks: those
+  // re-read the span's last block and are zeroed.
+  constexpr int G = BT + KT <= 4 ? 4 : BT + KT <= 6 ? 2 : 1;
+  for (int64_t sp = (int64_t)blockIdx.x * 4 + w; sp < spans; sp += (int64_t)gridDim.x * 4) {
+    const int64_t e_begin = sp * kDwSpan;
+    const int nit = (int)((min(L, e_begin + kDwSpan) - e_begin) / 16);   // (uniform; L is a multiple of 16)
+    for (int it0 = 0; it0 < nit; it0 += G) {
+      f4 a[G][BT], bb[G][KT];
 #pragma unroll
-    for (int u = 0; u < G; ++u) {
-      const bool live = it0 + u < nit;
-      const int64_t e = e_begin + (int64_t)min(it0 + u, nit - 1) * 16 + 4 * q;
-      // unconditional loads (row and block clamped into range), masked afterwards
+      for (int u = 0; u < G; ++u) {
+        const bool live = it0 + u < nit;
+        const int64_t e = e_begin + (int64_t)min(it0 + u, nit - 1) * 16 + 4 * q;
+        // unconditional loads (row and block clamped into range), masked afterwards
 #pragma unroll
-      for (int i = 0; i < MAXBT; ++i) {
-        const int b = 16 * i + x;
-        a[u][i] = *reinterpret_cast<const f4*>(draw + (int64_t)min(b, B - 1) * L + e);
-        if (!(live && i < nbt && b < B)) a[u][i] = zero;
+        for (int i = 0; i < BT; ++i) {
+          const int b = 16 * i + x;
+          a[u][i] = *reinterpret_cast<const f4*>(draw + (int64_t)min(b, B - 1) * L + e);
+          if (!(live && b < B)) a[u][i] = zero;
+        }
+#pragma unroll
+        for (int j = 0; j < KT; ++j) {
+          const int k = 16 * j + x + 1;
+          bb[u][j] = *reinterpret_cast<const f4*>(bases + (int64_t)min(k, K) * L + e);
+          if (!(live && k <= K)) bb[u][j] = zero;
+        }
+        if (q == 3) {                          // features 14 and 15 are pads
+#pragma unroll
+          for (int i = 0; i < BT; ++i) { a[u][i][2] = 0.f; a[u][i][3] = 0.f; }
+#pragma unroll
+          for (int j = 0; j < KT; ++j) { bb[u][j][2] = 0.f; bb[u][j][3] = 0.f; }
+        }
       }
+      __builtin_amdgcn_sched_barrier(0);      // keep the group's loads ahead of its products
 #pragma unroll
-      for (int j = 0; j < MAXKT; ++j) {
-        const int k = 16 * j + x + 1;
-        bb[u][j] = *reinterpret_cast<const f4*>(bases + (int64_t)min(k, K) * L + e);
-        if (!(live && j < nkt && k <= K)) bb[u][j] = zero;
-      }
-      if (q == 3) {                          // features 14 and 15 are pads
+      for (int u = 0; u < G; ++u)
 #pragma unroll
-        for (int i = 0; i < MAXBT; ++i) { a[u][i][2] = 0.f; a[u][i][3] = 0.f; }
+        for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int j = 0; j < MAXKT; ++j) { bb[u][j][2] = 0.f; bb[u][j][3] = 0.f; }
-      }
+          for (int i = 0; i < BT; ++i)
+#pragma unroll
+            for (int j = 0; j < KT; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][c], bb[u][j][c], acc[i][j], 0, 0, 0);
     }
-    __builtin_amdgcn_sched_barrier(0);      // keep the group's loads ahead of its products
+    if (!MULTI) break;
 #pragma unroll
-    for (int u = 0; u < G; ++u)
+    for (int i = 0; i < BT; ++i)
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int i = 0; i < MAXBT; ++i)
-#pragma unroll
-          for (int j = 0; j < MAXKT; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][c], bb[u][j][c], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < KT; ++j) {
+        sum[i][j] += acc[i][j];
+        acc[i][j] = zero;
+      }
   }
   // D layout of the f32 16x16x4 op: lane l, item r holds row 4(l/16) + r, column l%16.
-  if constexpr (MAXBT * MAXKT <= 2) {
-    // small tiles: the block's four waves are added in LDS (wave order) and
-    // the block writes one [B][K] partial
-    constexpr int TB = 16 * MAXBT, TK = 16 * MAXKT;
-    __shared__ float ws[4][TB * TK];
-    const int w = threadIdx.x >> 6;
+  float* out = partials + (int64_t)blockIdx.x * B * K;
 #pragma unroll
-    for (int i = 0; i < MAXBT; ++i)
+  for (int i = 0; i < BT; ++i)
 #pragma unroll
-      for (int j = 0; j < MAXKT; ++j)
+    for (int j = 0; j < KT; ++j) {
+      if (i + j) __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ws[w][(16 * i + 4 * q + r) * TK + 16 * j + x] = acc[i][j][r];
-    __syncthreads();
-    float* out = partials + (int64_t)blockIdx.x * B * K;
-    for (int t = threadIdx.x; t < B * K; t += 256) {
-      const int b = t / K, k = t % K;
-      const int o = b * TK + k;
-      out[t] = ((ws[0][o] + ws[1][o]) + ws[2][o]) + ws[3][o];
+      for (int r = 0; r < 4; ++r) ws[w][(4 * q + r) * 16 + x] = MULTI ? sum[i][j][r] : acc[i][j][r];
+      __syncthreads();
+      const int o = threadIdx.x, b = 16 * i + (o >> 4), k = 16 * j + (o & 15);
+      if (b < B && k < K) out[(int64_t)b * K + k] = ((ws[0][o] + ws[1][o]) + ws[2][o]) + ws[3][o];
     }
-  } else {
-    float* out = partials + gw * (int64_t)B * K;
-#pragma unroll
-    for (int i = 0; i < MAXBT; ++i)
-#pragma unroll
-      for (int j = 0; j < MAXKT; ++j)
-        if (i < nbt && j < nkt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int b = 16 * i + 4 * q + r;
-            const int k = 16 * j + x;
-            if (b < B && k < K) out[(int64_t)b * K + k] = acc[i][j][r];
-          }
-  }
 }
 
-// One block per output: each thread sums a fixed stride of the partials,
-// then a fixed-shape tree over the block.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partials, int64_t n_part,
-                                                              int BK, float* __restrict__ out, int accumulate) {
-  __shared__ float sm[256];
-  const int i = blockIdx.x;
+// A workgroup per 16 outputs, 64 partials side by side: a thread sums the
+// partials of its output 64 apart, 16 at a time in a tree (their loads in
+// flight together), then a fixed-shape tree over the 64.  16 consecutive
+// outputs are read as one 64-byte line.
+constexpr int kRedCols = 16, kRedRows = 64;
+
+__global__ __launch_bounds__(kRedCols * kRedRows) void reduce_partials_kernel(const float* __restrict__ partials,
+                                                                              int n_part, int BK,
+                                                                              float* __restrict__ out,
+                                                                              int accumulate) {
+  __shared__ float sm[kRedRows][kRedCols + 1];
+  const int c = threadIdx.x % kRedCols, r = threadIdx.x / kRedCols;
+  const int i = blockIdx.x * kRedCols + c, ic = min(i, BK - 1);
   float s = 0.0f;
-  for (int64_t p = threadIdx.x; p < n_part; p += 256) s += partials[p * BK + i];
-  sm[threadIdx.x] = s;
+  for (int p0 = r; p0 < n_part; p0 += 16 * kRedRows) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int p = p0 + u * kRedRows;
+      const float x = partials[(int64_t)min(p, n_part - 1) * BK + ic];
+      v[u] = p < n_part ? x : 0.0f;
+    }
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1)
+#pragma unroll
+      for (int u = 0; u < d; ++u) v[u] += v[u + d];
+    s += v[0];
+  }
+  sm[r][c] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) sm[threadIdx.x] += sm[threadIdx.x + w];
+  for (int d = kRedRows / 2; d > 0; d >>= 1) {
+    if (r < d) sm[r][c] += sm[r + d][c];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[i] = accumulate ? out[i] + sm[0] : sm[0];
+  if (r == 0 && i < BK) out[i] = accumulate ? out[i] + sm[0][c] : sm[0][c];
 }
 
 int64_t blend_bwd_partials(int B, int K, int64_t N) {
@@ -331,11 +347,34 @@ int64_t blend_bwd_partials(int B, int K, int64_t N) {
   return waves * (int64_t)B * K;
 }
 
+// (an upper bound: the launch writes one partial per workgroup, at most kDwBlocks of them)
 int64_t blend_bwd_partials_used(int B, int K, int64_t N) {
   if (K == 0) return 0;
   const int64_t blocks = (int64_t)div_up(N * kNF, 4 * kDwSpan);
-  const bool small = B <= 16 && K <= 32;     // as launch_blend_bwd: a partial per block, else per wave
+  const bool small = B <= 16 && K <= 32;
   return (small ? blocks : 4 * blocks) * (int64_t)B * K;
+}
+
+template <int BT, bool MULTI>
+static void launch_dweights(int blocks, const float* draw, const float* bases, int B, int K, int64_t N,
+                            float* partials, hipStream_t s) {
+  const dim3 g(blocks), t(256);
+#define GBR_DW(KT) \
+  hipLaunchKernelGGL((blend_dweights_kernel<BT, KT, MULTI>), g, t, 0, s, draw, bases, B, K, N, partials)
+  if (K <= 16) GBR_DW(1);
+  else if (K <= 32) GBR_DW(2);
+  else if (K <= 48) GBR_DW(3);
+  else GBR_DW(4);
+#undef GBR_DW
+}
+
+template <bool MULTI>
+static void launch_dweights(int blocks, const float* draw, const float* bases, int B, int K, int64_t N,
+                            float* partials, hipStream_t s) {
+  if (B <= 16) launch_dweights<1, MULTI>(blocks, draw, bases, B, K, N, partials, s);
+  else if (B <= 32) launch_dweights<2, MULTI>(blocks, draw, bases, B, K, N, partials, s);
+  else if (B <= 48) launch_dweights<3, MULTI>(blocks, draw, bases, B, K, N, partials, s);
+  else launch_dweights<4, MULTI>(blocks, draw, bases, B, K, N, partials, s);
 }
 
 void launch_blend_bwd(const float* draw, const float* bases, const float* weights, int B, int K, int64_t N,
@@ -349,16 +388,12 @@ void launch_blend_bwd(const float* draw, const float* bases, const float* weight
                          accumulate);
     });
   if (K == 0) return;
-  const dim3 g2(div_up(N * kNF, 4 * kDwSpan));
-  const bool small = B <= 16 && K <= 32;
-  if (small)
-    hipLaunchKernelGGL((blend_dweights_kernel<1, 2>), g2, dim3(256), 0, s, draw, bases, B, K, N, partials);
-  else
-    hipLaunchKernelGGL((blend_dweights_kernel<4, 4>), g2, dim3(256), 0, s, draw, bases, B, K, N, partials);
-  const int64_t n_part = (int64_t)g2.x * (small ? 1 : 4);   // a partial per block (small tiles) or per wave
+  const int all = div_up(N * kNF, 4 * kDwSpan), blocks = std::min(all, kDwBlocks);
+  if (all > blocks) launch_dweights<true>(blocks, draw, bases, B, K, N, partials, s);
+  else launch_dweights<false>(blocks, draw, bases, B, K, N, partials, s);
   (void)n_partials;
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(B * K), dim3(256), 0, s, partials, n_part, B * K, dweights,
-                     accumulate);
+  hipLaunchKernelGGL(reduce_partials_kernel, dim3(div_up(B * K, kRedCols)), dim3(kRedCols * kRedRows), 0, s, partials,
+                     blocks, B * K, dweights, accumulate);
 }
 
 }  // namespace gbr
