@@ -1,7 +1,7 @@
-// Per-frame depth order of the visible splats: every valid splat gets its
-// frame-local rank in ascending (binary32 depth, splat index) order, the
-// order in which the compositing visits Gaussians.  Done once per frame
-// instead of once per tile:
+// Per-frame depth order of the visible splats: a list of each frame's valid
+// splats in ascending (binary32 depth, splat index) order, the order in which
+// the compositing visits Gaussians.  Done once per frame instead of once per
+// tile:
 //   1. splats are distributed over nbk buckets per frame by their depth bits,
 //      scaled between the frame's min and max (monotone in depth);
 //   2. buckets are ranked by direct comparison, 32 buckets per workgroup
@@ -156,11 +156,11 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_scatter_kernel(PassArgs
   }
 }
 
-
-__device__ __forceinline__ void emit_ranked(const PassArgs& a, unsigned long long key, uint32_t pos, uint32_t vbase) {
-  const uint32_t s = (uint32_t)key;
-  a.depth_sorted[pos] = s;
-  a.rank[s] = pos - vbase;
+// The position is all that is kept.  (Each splat's position was also stored
+// by splat, scattered, and read by nothing: the ordering launch 14.5 -> 9.7 us
+// for 16 frames of 50k splats, 59 -> 42 for 64 of 100k.)
+__device__ __forceinline__ void emit_ranked(const PassArgs& a, unsigned long long key, uint32_t pos) {
+  a.depth_sorted[pos] = (uint32_t)key;
 }
 
 // Ranks within buckets.  Keys are unique, so a key's rank is the number of
@@ -209,7 +209,6 @@ __device__ void sort_large_buckets(const PassArgs& a, int s, int ns, unsigned lo
       const int g = (int)list[item];
       const uint32_t start = a.bkt_start[g];
       const int n = (int)(a.bkt_start[g + 1] - start);
-      const uint32_t vbase = a.bkt_start[(g / a.nbk) * a.nbk];
       __syncthreads();
       if (n <= kBigDirect) {
         for (int i = threadIdx.x; i < n; i += kOrderThreads) keys[i] = a.bkeys[start + i];
@@ -218,7 +217,7 @@ __device__ void sort_large_buckets(const PassArgs& a, int s, int ns, unsigned lo
           const unsigned long long k = keys[i];
           uint32_t rank = 0;
           for (int j = 0; j < n; ++j) rank += keys[j] < k ? 1u : 0u;
-          emit_ranked(a, k, start + rank, vbase);
+          emit_ranked(a, k, start + rank);
         }
       } else {
         unsigned long long* src = a.bkeys + start;
@@ -243,23 +242,21 @@ __device__ void sort_large_buckets(const PassArgs& a, int s, int ns, unsigned lo
           parity ^= 1;
         }
         const unsigned long long* out = parity ? alt : src;
-        for (int i = threadIdx.x; i < n; i += kOrderThreads) emit_ranked(a, out[i], start + (uint32_t)i, vbase);
+        for (int i = threadIdx.x; i < n; i += kOrderThreads) emit_ranked(a, out[i], start + (uint32_t)i);
       }
     }
     __syncthreads();   // the list is rewritten by the next round
   }
 }
 
-__device__ void rank_buckets(const PassArgs& a, int blk, unsigned long long* keys, uint32_t* bs, uint32_t* vb) {
+__device__ void rank_buckets(const PassArgs& a, int blk, unsigned long long* keys, uint32_t* bs) {
   const int nb = a.B * a.nbk;
   const int gb0 = blk * kRankBuckets;
   const int nbl = min(nb - gb0, kRankBuckets);
   if (threadIdx.x <= nbl) bs[threadIdx.x] = a.bkt_start[gb0 + threadIdx.x];
-  if (threadIdx.x == 0) *vb = a.bkt_start[(gb0 / a.nbk) * a.nbk];
   __syncthreads();
   const uint32_t k0 = bs[0], nk = bs[nbl] - k0;
   const uint32_t cap = nk <= (uint32_t)kRankKeys ? kRankMax : kWaveMax;
-  const uint32_t vbase = *vb;
   if (nk <= (uint32_t)kRankKeys) {
     for (uint32_t i = threadIdx.x; i < nk; i += kOrderThreads) keys[i] = a.bkeys[k0 + i];
     __syncthreads();
@@ -275,7 +272,7 @@ __device__ void rank_buckets(const PassArgs& a, int blk, unsigned long long* key
       const unsigned long long k = keys[i];
       uint32_t rank = 0;
       for (uint32_t j = j0; j < j1; ++j) rank += keys[j] < k ? 1u : 0u;
-      emit_ranked(a, k, k0 + j0 + rank, vbase);
+      emit_ranked(a, k, k0 + j0 + rank);
     }
     return;
   }
@@ -291,7 +288,7 @@ __device__ void rank_buckets(const PassArgs& a, int blk, unsigned long long* key
       const uint32_t klo = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)q);
       rank += (khi < hi || (khi == hi && klo < lo)) ? 1u : 0u;
     }
-    if (lane < (int)n) emit_ranked(a, key, start + rank, vbase);
+    if (lane < (int)n) emit_ranked(a, key, start + rank);
   }
 }
 
@@ -304,9 +301,8 @@ __global__ __launch_bounds__(kOrderThreads) void bucket_order_kernel(PassArgs a,
   __shared__ uint32_t list[kOrderThreads];
   __shared__ uint32_t nlist;
   __shared__ uint32_t bs[kRankBuckets + 1];
-  __shared__ uint32_t vb;
   if ((int)blockIdx.x < ns) sort_large_buckets(a, (int)blockIdx.x, ns, keys, hist, lds_waves, vary, list, &nlist);
-  else rank_buckets(a, (int)blockIdx.x - ns, keys, bs, &vb);
+  else rank_buckets(a, (int)blockIdx.x - ns, keys, bs);
 }
 
 void launch_depth_order(const PassArgs& a, int64_t max_frame_splats, uint32_t* scan_scratch, const ScanJob& side,

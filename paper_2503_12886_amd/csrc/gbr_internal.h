@@ -110,7 +110,6 @@ struct PassArgs {
   unsigned long long* bkeys;      // [S] (depth bits << 32) | splat, grouped by bucket
   unsigned long long* bkeys_alt;  // [S] ping-pong for large buckets
   uint32_t* depth_sorted;   // [S] valid splats of each frame in (depth, index) order
-  uint32_t* rank;           // [S] frame-local position of a valid splat in that order
   // pixel stage
   uint32_t* n_iter;         // [pixels] list position after the last contributor
   uint32_t* n_contrib;      // [pixels] number of contributors (computed on request)
