@@ -128,7 +128,7 @@ struct gbr_ctx {
   // per-frame depth order
   uint32_t *blk_mm = nullptr, *bkt_count = nullptr, *bkt_moff = nullptr, *bkt_start = nullptr;
   unsigned long long *bkeys = nullptr, *bkeys_alt = nullptr;
-  uint32_t *depth_sorted = nullptr;
+  uint32_t *depth_sorted = nullptr, *hits = nullptr;
   int64_t cap_bkt = 0, cap_bkt_cells = 0;
   int nbk = 64, nblk = 1;
   float* part = nullptr;
@@ -222,7 +222,7 @@ PassArgs make_args(gbr_ctx* c) {
   a.seg_stride = a.bitmap_words / a.seg_words;
   a.seg_cnt = c->seg_cnt;
   a.blk_mm = c->blk_mm; a.bkt_count = c->bkt_count; a.bkt_moff = c->bkt_moff; a.bkt_start = c->bkt_start;
-  a.bkeys = c->bkeys; a.bkeys_alt = c->bkeys_alt; a.depth_sorted = c->depth_sorted;
+  a.bkeys = c->bkeys; a.bkeys_alt = c->bkeys_alt; a.depth_sorted = c->depth_sorted; a.hits = c->hits;
   a.n_iter = c->n_iter; a.n_contrib = c->n_contrib; a.t_final = c->t_final; a.part = c->part;
   a.tg = c->tg;
   return a;
@@ -307,7 +307,7 @@ void free_all(gbr_ctx* c) {
   dfree(c->order_fwd); dfree(c->order_bwd); dfree(c->cls_cnt);
   dfree(c->sorted); dfree(c->part); dfree(c->part_flag); dfree(c->qmask);
   dfree(c->blk_mm); dfree(c->bkt_count); dfree(c->bkt_moff); dfree(c->bkt_start);
-  dfree(c->bkeys); dfree(c->bkeys_alt); dfree(c->depth_sorted);
+  dfree(c->bkeys); dfree(c->bkeys_alt); dfree(c->depth_sorted); dfree(c->hits);
   dfree(c->n_iter); dfree(c->n_contrib); dfree(c->t_final); dfree(c->scan_scratch); dfree(c->scan_scratch_splat);
   dfree(c->draw_scratch);
   dfree(c->ci_ones); dfree(c->ci_draw);
@@ -524,7 +524,7 @@ int64_t workspace_bytes(const WorkspaceCaps& k) {
   b += n(k.splats * kRecF) * 4 + n(k.splats) * 16 + n(k.splats) * 4 + n(k.splats + 1) * 4 + n(k.splats) * 4;
   b += (n(k.tiles) + n(k.tiles + 1) + n(k.tiles) + n(4 * k.tiles) + 2 * n(33 * k.tiles)) * 4 + 66 * 4;
   b += n(2 * ((int64_t)div_up(k.splats, 256) + k.frames + 1)) * 4;   // projection workgroups' depth ranges
-  b += (n(k.splats) * 2) * 8 + n(k.splats) * 4;                           // bucket keys, order
+  b += (n(k.splats) * 2) * 8 + n(k.splats) * 4 * 2;                       // bucket keys, order, hits
   b += (n(k.bkt_cells) + n(k.bkt_cells + 1) + n(k.bkt + 1)) * 4;  // depth buckets
   b += 3 * n(k.pixels) * 4;                                                  // n_iter, n_contrib, t_final
   b += n(k.scan_words) * 4 + n(scan_scratch_words(k.splats)) * 4 + n(k.splats * kNF) * 4;
@@ -627,6 +627,7 @@ int gbr_create(const gbr_config* cfg, gbr_ctx** out) {
   TRY(dalloc(&c->bkeys, c->cap_splats));
   TRY(dalloc(&c->bkeys_alt, c->cap_splats));
   TRY(dalloc(&c->depth_sorted, c->cap_splats));
+  TRY(dalloc(&c->hits, c->cap_splats));
   TRY(alloc_buckets(c, 64LL * c->cap_frames, 64LL * c->cap_frames));
   TRY(dalloc(&c->n_iter, c->cap_pixels));
   TRY(dalloc(&c->n_contrib, c->cap_pixels));

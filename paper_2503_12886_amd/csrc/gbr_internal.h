@@ -102,14 +102,15 @@ struct PassArgs {
   int32_t seg_words;        // words per row segment (8 or 16); a segment's set bits are counted once
   int32_t seg_stride;       // segments per row = bitmap_words / seg_words
   uint32_t* blk_mm;         // [2 per projection workgroup] min, max binary32 depth bits of its valid splats;
-                            // frame b's workgroup j at gauss_base / 256 + b + j (frames never share one)
-                            //   (a 128-byte line per frame, so frames' atomics do not share a line)
+                            // frame b's workgroup j at gauss_base / 256 + b + j (frames never share one);
+                            // the backward pass leaves the workgroup's number of hits in the first word
   uint32_t* bkt_count;      // [B * nbk][nblk] per-block bucket counts
   uint32_t* bkt_moff;       // [B * nbk * nblk + 1] their exclusive scan
   uint32_t* bkt_start;      // [B * nbk + 1] exclusive scan; frame b's valid splats start at bkt_start[b * nbk]
   unsigned long long* bkeys;      // [S] (depth bits << 32) | splat, grouped by bucket
   unsigned long long* bkeys_alt;  // [S] ping-pong for large buckets
   uint32_t* depth_sorted;   // [S] valid splats of each frame in (depth, index) order
+  uint32_t* hits;           // [S] backward: per projection workgroup, its splats with a gradient (frame-local index)
   // pixel stage
   uint32_t* n_iter;         // [pixels] list position after the last contributor
   uint32_t* n_contrib;      // [pixels] number of contributors (computed on request)

@@ -601,106 +601,164 @@ void launch_composite_bwd(const PassArgs& a, const float* dimages, const float* 
 }
 
 // ---------------------------------------------------------------- gather + projection adjoint
-// One thread per splat.  It sums its entries' partials in row-major tile
-// order (unflagged entries -- no contributing pixel, or past the tile's last
-// used position -- are zero): the flags of a 64-entry window are read as four
-// 16-byte loads, then the flagged partials 4 at a time, all loads in flight
-// before any is used, and each consumed flag is reset to 0 for the next
-// pass.  It then chains the 9 sums back through the conic, the EWA
-// projection and the activations in float64 and writes the splat's draw
-// row.  (As two passes, the sums written to the row and read back, it took
-// 12 us more: the adjoint's lower occupancy hides the gather's loads well
-// enough.)
+// A splat's entries' partials are summed in row-major tile order (unflagged
+// entries -- no contributing pixel, or past the tile's last used position --
+// are zero), each flag read is reset to 0 for the next pass, and the 9 sums
+// are chained back through the conic, the EWA projection and the activations
+// in float64 into the splat's draw row.
+//
+// Batches of kTwoPassSplats splats or more do it in two passes.  The gather
+// writes every splat's sums to its row and lists the splats with a flagged
+// entry, a list per workgroup: most splats lie behind the ones that stop the
+// pixels and have none (half to four fifths of those measured).  The adjoint,
+// a wave per list, rewrites the listed splats' rows.  The entries of a wave's
+// 64 splats are one run of emission slots, which the wave gathers together:
+// flags 16 to a lane (1024 entries a window); the flagged entries listed in
+// LDS; their 48-byte partials fetched by three lanes each, 21 to a load, and
+// added from LDS by the splat's lane; the rows written as one run.  With a
+// thread reading its own splat's flags, partials and row, five times as many
+// memory instructions are issued, most of their lanes idle or on lines of
+// their own, and their issue bounds the pass.  Smaller batches keep that form,
+// one launch: the second launch's latencies cost more than it saves.
+// Measured, one launch against two (us): 100k splats 18 / 22, 150k 15 / 21,
+// 500k 47 / 44, 600k (half of them listed) 89 / 80, 800k 76 / 64, 6.4M
+// 361 / 287.
+constexpr int64_t kTwoPassSplats = 500000;
+
 // Flag bytes (0 or 1) of 4 entries -> 4 bits.
 __device__ __forceinline__ uint32_t flag_nibble(uint32_t w) {
   return (w & 1u) | ((w >> 7) & 2u) | ((w >> 14) & 4u) | ((w >> 21) & 8u);
 }
 
-// The 9 sums of a splat over its c entries from off on (acc zeroed by the caller).
-__device__ __forceinline__ void gather_splat_sums(const PassArgs& a, uint32_t off, uint32_t c, float (&acc)[9]) {
-  const uint32_t end = off + c;
-  const uint32_t* fw = reinterpret_cast<const uint32_t*>(a.part_flag);   // padded by 64 bytes past the capacity
-  // windows of 64 entries starting at a multiple of 16: the 16 flag words
-  // are read as four aligned 16-byte loads and turned into a bit mask of
-  // the flagged entries, whose partials are then read 4 at a time (all 4
-  // in flight together)
-  for (uint32_t e0 = off & ~15u; e0 < end; e0 += 64) {
-    uint32_t w[16];
-    const uint4* fq = reinterpret_cast<const uint4*>(fw + (e0 >> 2));
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint4 x = fq[k];
-      w[4 * k] = x.x; w[4 * k + 1] = x.y; w[4 * k + 2] = x.z; w[4 * k + 3] = x.w;
-    }
-    unsigned long long m = 0ull;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) m |= (unsigned long long)flag_nibble(w[k]) << (4 * k);
-    // keep [off, end) only
-    const uint32_t lo = off > e0 ? off - e0 : 0u;
-    const uint32_t hi = end - e0 < 64u ? end - e0 : 64u;
-    m &= (hi >= 64u ? ~0ull : ((1ull << hi) - 1ull)) & ~((1ull << lo) - 1ull);
-    while (m) {
-      uint32_t e[4];
-      bool v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        v[u] = m != 0ull;
-        e[u] = v[u] ? e0 + (uint32_t)(__ffsll((long long)m) - 1) : off;   // off: in range, unused
-        m &= m - 1ull;
-      }
-      float4 q[4][3];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float4* src = reinterpret_cast<const float4*>(a.part + (int64_t)e[u] * kPartF);
-        q[u][0] = src[0]; q[u][1] = src[1]; q[u][2] = src[2];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (!v[u]) continue;
-        // the flag goes back to 0 for the next pass (only this splat's
-        // flags are written; neighbours mask this entry out of their windows)
-        a.part_flag[e[u]] = 0;
-        acc[0] += q[u][0].x; acc[1] += q[u][0].y; acc[2] += q[u][0].z; acc[3] += q[u][0].w;
-        acc[4] += q[u][1].x; acc[5] += q[u][1].y; acc[6] += q[u][1].z; acc[7] += q[u][1].w;
-        acc[8] += q[u][2].x;
-      }
-    }
-  }
-}
+constexpr int kGatherThreads = 256;       // splats per list: the projection's workgroups
+constexpr int kGatherWindow = 1024;       // entries whose flags a wave reads at once
+constexpr int kGatherStage = 63;          // partials a wave stages at once: three rounds of 21
 
-// A workgroup per (frame, 64 of its splats): the frame is the grid's y
-// index, so its camera is read at uniform addresses.  One-wave workgroups
-// let the chip's last round of waves be filled finely (the splats' gathers
-// differ in length).
-constexpr int kAdjThreads = 64;
-__global__ __launch_bounds__(kAdjThreads) void proj_adjoint_kernel(PassArgs a, const float* __restrict__ raw,
-                                                                   float* __restrict__ draw) {
+struct GatherWave {
+  float4 stage[64 * 4];                   // partials (3 to an entry), then the draw rows
+  uint16_t hit[kGatherWindow];            // the window's flagged entries, from its first slot
+  uint16_t bits[64];                      // the flags of each lane's 16 entries
+  uint16_t before[64];                    // and the flagged entries before them
+};
+
+__global__ __launch_bounds__(kGatherThreads) void gather_sums_kernel(PassArgs a, float* __restrict__ draw) {
+  __shared__ GatherWave gw[kGatherThreads / 64];
+  __shared__ uint32_t wn[kGatherThreads / 64];
   const int b = blockIdx.y;
   const FrameDev& F = a.frames[b];
-  const int64_t n = (int64_t)blockIdx.x * kAdjThreads + threadIdx.x;
-  if (n >= F.gauss_count) return;
-  const int64_t s = F.gauss_base + n;
-  float4* out = reinterpret_cast<float4*>(draw + s * kNF);
-  // the overflow flag, the count, the entry offset and the splat's blended
-  // Gaussian are read together, so that one load latency precedes the
-  // gather instead of three
-  const uint32_t ovf = a.status->overflow, c = a.cnt[s], off = a.soff[s];
-  const float4* src = reinterpret_cast<const float4*>(raw + s * kNF);
-  float4 v0 = src[0], v1 = src[1];
-  const float4 v2 = src[2];
-  // (an empty use before the branch, or the compiler sinks the last two
-  // loads past it and waits for the count first)
-  asm volatile("" ::"v"(ovf), "v"(off), "v"(v0.x), "v"(v0.y), "v"(v0.z), "v"(v0.w), "v"(v1.x), "v"(v1.y), "v"(v1.z),
-               "v"(v1.w), "v"(v2.x), "v"(v2.y), "v"(v2.z));
-  if (ovf || c == 0) {
-    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    out[0] = z; out[1] = z; out[2] = z; out[3] = z;
-    return;
-  }
+  const int64_t n0 = (int64_t)blockIdx.x * kGatherThreads;
+  if (n0 >= F.gauss_count) return;          // (uniform)
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  GatherWave& G = gw[w];
+  const int64_t nw = n0 + w * 64;           // the wave's first splat
+  const int rows = (int)min((int64_t)64, F.gauss_count - nw);   // (may be negative: nothing to do)
+  const int64_t s = F.gauss_base + min(nw + lane, F.gauss_count - 1);
+  const uint32_t ovf = a.status->overflow;
+  const uint32_t off = a.soff[s], cnt = lane < rows ? a.cnt[s] : 0u;
   float acc[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = 0.0f;
-  gather_splat_sums(a, off, c, acc);
+  bool any = false;
+  if (rows > 0 && !ovf) {
+    const uint32_t first = __builtin_amdgcn_readlane((int)off, 0);
+    const uint32_t end = __builtin_amdgcn_readlane((int)(off + cnt), rows - 1);
+    for (uint32_t e0 = first & ~15u; e0 < end; e0 += kGatherWindow) {
+      // ---- the window's flags: 16 to a lane, read and cleared ----
+      const uint32_t el = e0 + 16u * (uint32_t)lane;
+      uint32_t m = 0u;
+      if (el < end) {
+        uint4* fl = reinterpret_cast<uint4*>(a.part_flag + el);   // (padded by 64 bytes past the capacity)
+        const uint4 x = *fl;
+        m = flag_nibble(x.x) | flag_nibble(x.y) << 4 | flag_nibble(x.z) << 8 | flag_nibble(x.w) << 12;
+        // only this wave's entries; the others' flags stay
+        const uint32_t lo = first > el ? first - el : 0u, hi = min(end - el, 16u);
+        m &= ((1u << hi) - 1u) & ~((1u << lo) - 1u);
+        if (m != 0u) {
+          if (lo == 0u && hi == 16u) {
+            *fl = make_uint4(0u, 0u, 0u, 0u);
+          } else {
+            for (uint32_t r = m; r != 0u; r &= r - 1u) a.part_flag[el + (uint32_t)__builtin_ctz(r)] = 0;
+          }
+        }
+      }
+      const uint32_t c = __popc(m), inc = wave_incl_scan(c);
+      const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+      if (total == 0u) continue;
+      wave_sync();
+      G.bits[lane] = (uint16_t)m;
+      G.before[lane] = (uint16_t)(inc - c);
+      uint32_t at = inc - c;
+      for (uint32_t r = m; r != 0u; r &= r - 1u) G.hit[at++] = (uint16_t)(16 * lane + __builtin_ctz(r));
+      wave_sync();
+      // ---- this splat's flagged entries: [h0, h1) of the window's ----
+      auto place = [&](uint32_t e) -> uint32_t {   // flagged entries before slot e
+        if (e <= e0) return 0u;
+        const uint32_t d = e - e0;
+        if (d >= (uint32_t)kGatherWindow) return total;
+        return G.before[d >> 4] + (uint32_t)__popc(G.bits[d >> 4] & ((1u << (d & 15u)) - 1u));
+      };
+      const uint32_t h0 = place(off), h1 = cnt ? place(off + cnt) : h0;
+      any |= h1 > h0;
+      // ---- their partials, staged and added in slot order; a round's are
+      // on their way while the round before is added ----
+      auto piece = [&](uint32_t g0, int j) -> float4 {   // piece t % 3 of entry g0 + t / 3, t = 63 j + lane
+        const uint32_t t = (uint32_t)(63 * j + min(lane, 62)), r = min(g0 + t / 3u, total - 1u);
+        return reinterpret_cast<const float4*>(a.part + (int64_t)(e0 + G.hit[r]) * kPartF)[t % 3u];
+      };
+      float4 x0 = piece(0, 0), x1 = piece(0, 1), x2 = piece(0, 2);
+      for (uint32_t g0 = 0; g0 < total; g0 += kGatherStage) {
+        wave_sync();
+        if (lane < 63) {
+          G.stage[lane] = x0;
+          G.stage[63 + lane] = x1;
+          G.stage[126 + lane] = x2;
+        }
+        wave_sync();
+        const uint32_t g1 = g0 + kGatherStage;
+        if (g1 < total) { x0 = piece(g1, 0); x1 = piece(g1, 1); x2 = piece(g1, 2); }
+        const uint32_t hb = min(max(h0, g0), g1), he = min(max(h1, g0), g1);
+        for (uint32_t h = hb; h < he; ++h) {
+          const float4* q = G.stage + 3u * (h - g0);
+          const float4 q0 = q[0], q1 = q[1];
+          acc[0] += q0.x; acc[1] += q0.y; acc[2] += q0.z; acc[3] += q0.w;
+          acc[4] += q1.x; acc[5] += q1.y; acc[6] += q1.z; acc[7] += q1.w;
+          acc[8] += q[2].x;
+        }
+      }
+    }
+  }
+  // ---- the draw rows, a contiguous run of memory ----
+  wave_sync();
+  G.stage[4 * lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  G.stage[4 * lane + 1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+  G.stage[4 * lane + 2] = make_float4(acc[8], 0.f, 0.f, 0.f);
+  G.stage[4 * lane + 3] = make_float4(0.f, 0.f, 0.f, 0.f);
+  wave_sync();
+  if (rows > 0) {
+    float4* out = reinterpret_cast<float4*>(draw + (F.gauss_base + nw) * kNF);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (64 * j + lane < 4 * rows) out[64 * j + lane] = G.stage[64 * j + lane];
+  }
+  // ---- the workgroup's splats with a gradient, in order ----
+  const unsigned long long m = __ballot(any);
+  if (lane == 0) wn[w] = (uint32_t)__popcll(m);
+  __syncthreads();
+  uint32_t at = lanes_below(m);
+  for (int i = 0; i < w; ++i) at += wn[i];
+  if (any) a.hits[F.gauss_base + n0 + at] = (uint32_t)(nw + lane);
+  if (threadIdx.x == kGatherThreads - 1)
+    a.blk_mm[2 * (F.gauss_base / kGatherThreads + b + blockIdx.x)] = at + (any ? 1u : 0u);
+}
+
+constexpr int kAdjThreads = 64;
+
+// The adjoint of frame b's splat n: v0, v1, v2 the first three float4 of its
+// blended record, acc its sums.
+__device__ __forceinline__ void splat_adjoint(const PassArgs& a, const FrameDev& F, int b, int64_t n, float4 v0,
+                                              float4 v1, const float4 v2, const float (&acc)[9],
+                                              float* __restrict__ draw) {
+  float4* out = reinterpret_cast<float4*>(draw + (F.gauss_base + n) * kNF);
 
   // ---- recompute the forward quantities (float64) ----
   if (a.tg.on) tangent_deform(a.tg, b, n, v0, v1, v0, v1);   // as the forward pass did
@@ -813,6 +871,114 @@ __global__ __launch_bounds__(kAdjThreads) void proj_adjoint_kernel(PassArgs a, c
   out[3] = make_float4(res[12], res[13], res[14], res[15]);
 }
 
+// A wave per list (a wave per 64 of its splats costs more in empty waves than
+// the longer lists' second rounds); the frame is the grid's y index, so its
+// camera is read at uniform addresses.
+__global__ __launch_bounds__(kAdjThreads, 3) void proj_adjoint_kernel(PassArgs a, const float* __restrict__ raw,
+                                                                      float* __restrict__ draw) {
+  const int b = blockIdx.y;
+  const FrameDev& F = a.frames[b];
+  const int64_t n0 = (int64_t)blockIdx.x * kGatherThreads;
+  if (n0 >= F.gauss_count) return;
+  const uint32_t count = a.blk_mm[2 * (F.gauss_base / kGatherThreads + b + blockIdx.x)];
+  for (uint32_t i = threadIdx.x; i < count; i += kAdjThreads) {
+    const int64_t n = a.hits[F.gauss_base + n0 + i], s = F.gauss_base + n;
+    const float4* g = reinterpret_cast<const float4*>(draw + s * kNF);
+    const float4* src = reinterpret_cast<const float4*>(raw + s * kNF);
+    const float4 g0 = g[0], g1 = g[1], g2 = g[2], v0 = src[0], v1 = src[1], v2 = src[2];
+    const float acc[9] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w, g2.x};
+    splat_adjoint(a, F, b, n, v0, v1, v2, acc, draw);
+  }
+}
+
+// The one-launch form, a thread per splat.
+// The 9 sums of a splat over its c entries from off on (acc zeroed by the caller).
+__device__ __forceinline__ void gather_splat_sums(const PassArgs& a, uint32_t off, uint32_t c, float (&acc)[9]) {
+  const uint32_t end = off + c;
+  const uint32_t* fw = reinterpret_cast<const uint32_t*>(a.part_flag);   // padded by 64 bytes past the capacity
+  // windows of 64 entries starting at a multiple of 16: the 16 flag words
+  // are read as four aligned 16-byte loads and turned into a bit mask of
+  // the flagged entries, whose partials are then read 4 at a time (all 4
+  // in flight together)
+  for (uint32_t e0 = off & ~15u; e0 < end; e0 += 64) {
+    uint32_t w[16];
+    const uint4* fq = reinterpret_cast<const uint4*>(fw + (e0 >> 2));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint4 x = fq[k];
+      w[4 * k] = x.x; w[4 * k + 1] = x.y; w[4 * k + 2] = x.z; w[4 * k + 3] = x.w;
+    }
+    unsigned long long m = 0ull;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) m |= (unsigned long long)flag_nibble(w[k]) << (4 * k);
+    // keep [off, end) only
+    const uint32_t lo = off > e0 ? off - e0 : 0u;
+    const uint32_t hi = end - e0 < 64u ? end - e0 : 64u;
+    m &= (hi >= 64u ? ~0ull : ((1ull << hi) - 1ull)) & ~((1ull << lo) - 1ull);
+    while (m) {
+      uint32_t e[4];
+      bool v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        v[u] = m != 0ull;
+        e[u] = v[u] ? e0 + (uint32_t)(__ffsll((long long)m) - 1) : off;   // off: in range, unused
+        m &= m - 1ull;
+      }
+      float4 q[4][3];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float4* src = reinterpret_cast<const float4*>(a.part + (int64_t)e[u] * kPartF);
+        q[u][0] = src[0]; q[u][1] = src[1]; q[u][2] = src[2];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (!v[u]) continue;
+        // the flag goes back to 0 for the next pass (only this splat's
+        // flags are written; neighbours mask this entry out of their windows)
+        a.part_flag[e[u]] = 0;
+        acc[0] += q[u][0].x; acc[1] += q[u][0].y; acc[2] += q[u][0].z; acc[3] += q[u][0].w;
+        acc[4] += q[u][1].x; acc[5] += q[u][1].y; acc[6] += q[u][1].z; acc[7] += q[u][1].w;
+        acc[8] += q[u][2].x;
+      }
+    }
+  }
+}
+
+// A workgroup per (frame, 64 of its splats): the frame is the grid's y
+// index, so its camera is read at uniform addresses.  One-wave workgroups
+// let the chip's last round of waves be filled finely (the splats' gathers
+// differ in length).
+__global__ __launch_bounds__(kAdjThreads) void gather_adjoint_kernel(PassArgs a, const float* __restrict__ raw,
+                                                                   float* __restrict__ draw) {
+  const int b = blockIdx.y;
+  const FrameDev& F = a.frames[b];
+  const int64_t n = (int64_t)blockIdx.x * kAdjThreads + threadIdx.x;
+  if (n >= F.gauss_count) return;
+  const int64_t s = F.gauss_base + n;
+  float4* out = reinterpret_cast<float4*>(draw + s * kNF);
+  // the overflow flag, the count, the entry offset and the splat's blended
+  // Gaussian are read together, so that one load latency precedes the
+  // gather instead of three
+  const uint32_t ovf = a.status->overflow, c = a.cnt[s], off = a.soff[s];
+  const float4* src = reinterpret_cast<const float4*>(raw + s * kNF);
+  float4 v0 = src[0], v1 = src[1];
+  const float4 v2 = src[2];
+  // (an empty use before the branch, or the compiler sinks the last two
+  // loads past it and waits for the count first)
+  asm volatile("" ::"v"(ovf), "v"(off), "v"(v0.x), "v"(v0.y), "v"(v0.z), "v"(v0.w), "v"(v1.x), "v"(v1.y), "v"(v1.z),
+               "v"(v1.w), "v"(v2.x), "v"(v2.y), "v"(v2.z));
+  if (ovf || c == 0) {
+    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    out[0] = z; out[1] = z; out[2] = z; out[3] = z;
+    return;
+  }
+  float acc[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) acc[k] = 0.0f;
+  gather_splat_sums(a, off, c, acc);
+  splat_adjoint(a, F, b, n, v0, v1, v2, acc, draw);
+}
+
 // ---------------------------------------------------------------- colour initialisation (Eq. 3)
 // draw_i / draw_1: the colour adjoint of the last render under the target
 // images and under all-ones images, i.e. per (frame, Gaussian) the sums of
@@ -847,8 +1013,14 @@ void launch_color_init_apply(const float* draw_i, const float* draw_1, int B, in
 
 void launch_gather_bwd(const PassArgs& a, const float* raw, float* draw, int64_t max_frame_splats, hipStream_t s) {
   if (a.n_splats == 0 || max_frame_splats == 0) return;
-  hipLaunchKernelGGL(proj_adjoint_kernel, dim3(div_up(max_frame_splats, kAdjThreads), a.B), dim3(kAdjThreads), 0, s, a,
-                     raw, draw);
+  if (a.n_splats < kTwoPassSplats) {
+    hipLaunchKernelGGL(gather_adjoint_kernel, dim3(div_up(max_frame_splats, kAdjThreads), a.B), dim3(kAdjThreads), 0, s,
+                       a, raw, draw);
+    return;
+  }
+  const dim3 grid(div_up(max_frame_splats, kGatherThreads), a.B);
+  hipLaunchKernelGGL(gather_sums_kernel, grid, dim3(kGatherThreads), 0, s, a, draw);
+  hipLaunchKernelGGL(proj_adjoint_kernel, grid, dim3(kAdjThreads), 0, s, a, raw, draw);
 }
 
 // ---------------------------------------------------------------- loss
