@@ -23,6 +23,21 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
   return dpp_add_u32<0x143, 0xc>(v);   // row_bcast:31
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_u32(uint32_t v) {
+  return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+// The OR of a value over the wave's lanes, on the scalar unit.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+  v = dpp_or_u32<0x111, 0xf>(v);   // row_shr:1
+  v = dpp_or_u32<0x112, 0xf>(v);
+  v = dpp_or_u32<0x114, 0xf>(v);
+  v = dpp_or_u32<0x118, 0xf>(v);
+  v = dpp_or_u32<0x142, 0xa>(v);   // row_bcast:15
+  v = dpp_or_u32<0x143, 0xc>(v);   // row_bcast:31
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // Orders the wave's LDS accesses across its lanes (they execute in program
 // order; this keeps the compiler from moving them).
 __device__ __forceinline__ void wave_sync() {

@@ -615,6 +615,28 @@ __device__ __forceinline__ bool strip_reach(float4 r0, float4 r1, float x0, floa
   return !(pa < thr) || !(pb < thr);
 }
 
+// The rectangle of the pixel centres of the lanes in M, the quadrant's first
+// at (qx0, qy0): lanes are 8 per row, so a column runs if any of its 8 lanes
+// does, a row if its byte of the wave mask is nonzero.
+template <int PXW>
+__device__ __forceinline__ void running_rect(unsigned long long M, float qx0, float qy0, float& sx0, float& sx1,
+                                             float& sy0, float& sy1) {
+  unsigned long long cm8 = M | (M >> 32);
+  cm8 |= cm8 >> 16;
+  cm8 |= cm8 >> 8;
+  cm8 &= 0xffull;
+  unsigned long long rm = M | (M >> 4);
+  rm |= rm >> 2;
+  rm |= rm >> 1;
+  rm &= 0x0101010101010101ull;
+  const int c0l = __ffsll((long long)cm8) - 1, c1l = 63 - __clzll((long long)cm8);
+  const int r0l = (__ffsll((long long)rm) - 1) >> 3, r1l = (63 - __clzll((long long)rm)) >> 3;
+  sx0 = qx0 + (float)(c0l * PXW);
+  sx1 = qx0 + (float)(c1l * PXW + PXW - 1);
+  sy0 = qy0 + (float)(r0l * PXW);
+  sy1 = qy0 + (float)(r1l * PXW + PXW - 1);
+}
+
 // alpha of a splat at a pixel, bit-identical wherever it is evaluated:
 // power = ca dx^2 + cb dx dy + cc dy^2 (= -q/2 in log2 units) plus lo =
 // log2(opacity), clamped at lo (q >= 0), and alpha = 2^power = o 2^(-q/2 log2 e).
@@ -635,13 +657,56 @@ __device__ __forceinline__ float splat_alpha(float4 r0, float cc, float lo, floa
   return __builtin_amdgcn_exp2f(pc);
 }
 
-// A staged candidate: mean, log2-scaled conic, log2 opacity, and then what
-// the blending alone reads: colour, and the position after it in the tile's list.
-struct __align__(16) StagedRec {
-  float4 r0;    // mx my ca cb
-  float2 r1;    // cc lo (lo = log2 opacity)
-  float pad[2];
-  float4 c;     // r g b, next (bits): list position after this entry
+// min(alpha, 0.99) of the same.  v_exp_f32 gives 0.99f itself at kAlphaMaxLog2
+// (and some 45 float32 to either side), no more below and no less above, so the
+// clamp goes to the power, where it is an operand of the minimum that is
+// taken anyway.
+constexpr float kAlphaMaxLog2 = -0.014499555f;
+__device__ __forceinline__ float clamped_alpha(float4 r0, float cc, float lo, float px, float py) {
+#pragma clang fp contract(off)
+  const float dx = px - r0.x, dy = py - r0.y;
+  float pw = __builtin_fmaf(r0.z * dx, dx, lo);
+  pw = __builtin_fmaf(r0.w * dx, dy, pw);
+  pw = __builtin_fmaf(cc * dy, dy, pw);
+  float pc;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(pc) : "v"(pw), "v"(lo), "s"(kAlphaMaxLog2));
+  return __builtin_amdgcn_exp2f(pc);
+}
+
+// The front-to-back step of an entry at a pixel: w is its alpha, or -0 where
+// that is below 1/255 (the entry is skipped, Te passes unchanged).
+// T (1 - alpha) < 1e-4 stops the pixel before this entry (Te -> -T); a stopped
+// pixel has Te <= 0, so its tn <= 0 stops it again (Te kept: -|Te|) and it
+// takes nothing.  Returns minus the entry's weight: negative where it is
+// taken, else +0, so that its sign is the pixel's bit, which goes to took.
+__device__ __forceinline__ float fold_step(float w, float& Te, uint32_t& took) {
+  const float tn = __builtin_fmaf(-w, Te, Te);   // T (1 - alpha), rounded once
+  const bool stop = tn < kTMin;
+  const float nw = stop ? 0.0f : -w * Te;
+  Te = stop ? -fabsf(Te) : tn;                   // one select with source modifiers
+  took = __builtin_amdgcn_alignbit(took, __float_as_uint(nw), 31);
+  return nw;
+}
+
+// Four staged candidates, in the nine 16-byte words that the wave reads them
+// in (every lane the same): mean and conic's first two terms of each; (cc, lo)
+// of each, lo = log2 opacity; colours.  The reads cost the LDS unit 5.7 cycles
+// a word of 16 bytes, 4.7 of 8 and 11.3 of 12, shared by a CU's waves, which
+// is as much as the blending takes of the vector units.
+struct __align__(16) FwdGroup {
+  static constexpr int N = 4;
+  float4 v[9];
+  __device__ __forceinline__ void put(int u, float4 q0, float4 q1, float qb) {
+    float* f = reinterpret_cast<float*>(v);
+    v[u] = q0;
+    *reinterpret_cast<float2*>(f + 16 + 2 * u) = make_float2(q1.x, q1.y);
+    f[24 + 3 * u] = q1.z; f[25 + 3 * u] = q1.w; f[26 + 3 * u] = qb;
+  }
+  __device__ __forceinline__ void pad(int u) {
+    float* f = reinterpret_cast<float*>(v);
+    f[17 + 2 * u] = -1e30f;
+    f[24 + 3 * u] = 0.f; f[25 + 3 * u] = 0.f; f[26 + 3 * u] = 0.f;
+  }
 };
 
 // One wave per (tile, quadrant): each wave composites its quadrant's pixels
@@ -656,9 +721,7 @@ struct __align__(16) StagedRec {
 // batches are in flight: while batch i is composited, the records of batch
 // i + 1 and the splat indices of batch i + 2 are on their way, so that the
 // chain segment counts -> words -> rank -> splat -> record costs its four
-// load latencies once per tile and not once per batch.  That chain bounds a
-// frame rendered alone: the chip holds all its waves at once and the longest
-// tile's serial walk is the pass's time.
+// load latencies once per tile and not once per batch.
 //
 // The entries of a batch whose alpha >= 1/255 region may reach the wave's
 // running pixels are compacted into LDS in list order (a lane tests an
@@ -666,30 +729,126 @@ struct __align__(16) StagedRec {
 // uniform counter.  Per (entry, pixel) the front-to-back step is written on
 // the pixel's signed transmittance Te (its transmittance while it runs; once
 // it has stopped, minus the transmittance at the stop), so every decision is
-// a vector compare and select: no per-entry mask logic on the scalar unit.
-// Entries behind the wave's stop are not composited; at most two batches of
-// them are read.  The consumed part of the sorted list is written out for
-// the backward pass (the quadrant waves of a tile write identical values),
-// with a 64-bit mask per batch of the entries that the quadrant took and the
-// quadrant's last used position.  The quadrant waves of a tile get block indices of the same
-// residue mod 8, so that they run on one XCD and share its L2.
+// a vector compare and select; which entries a pixel took is kept in a word a
+// lane, from which the wave's mask and the pixel's last position follow once
+// in 32 entries.  Entries behind the wave's stop are not
+// composited; at most two batches of them are read.  The consumed part of the
+// sorted list is written out for the backward pass (the quadrant waves of a
+// tile write identical values), with a 64-bit mask per batch of the entries
+// that the quadrant took and the quadrant's last used position.  The quadrant
+// waves of a tile get block indices of the same residue mod 8, so that they
+// run on one XCD and share its L2.
 //
 // Measured (us, against a batch read through its four latencies in turn, the
 // words of straddling segments read and emitted twice): one 512 x 512 frame
-// of 50k Gaussians 117 -> 84, 16 of them 223 -> 218 (bound by instruction
-// issue), 10 mesh-bound frames 353 -> 275, 64 uneven frames of 100k 1044 ->
-// 980.  Three entries at a time and 6 waves a SIMD: four at 5 waves gain
-// another 1 % on the longest lists and lose 1 % on full batches, two at 7
-// waves the reverse.  Waves of long lists at a raised issue priority: slower.
+// of 50k Gaussians 117 -> 84, 16 of them 223 -> 218, 10 mesh-bound frames 353
+// -> 275, 64 uneven frames of 100k 1044 -> 980.  With the clamp in the power,
+// the takes as sign bits per lane (they were a wave mask, a select and two
+// scalar operations an entry) and four entries in nine words (three, in eight
+// reads of 8 or 16 bytes): 84 -> 78, 217 -> 209, 267 -> 256, 960 -> 960.  16
+// frames issue 110 million vector instructions, 185 us of the 209.  Three
+// entries at a time, 72 registers and 7 waves a SIMD: 84, 207, 270, 1009.
+// Waves of long lists at a raised issue priority: slower.
 constexpr int kFwdBatch = 64;
 constexpr uint32_t kFwdRing = 256;   // a power of two >= 64 + 32: a whole word fits behind a batch
+
+// The stream of a tile's depth ranks (see the compositing below), run by one wave.
+struct RankStream {
+  const uint32_t* row;
+  const uint16_t* segc;
+  const uint32_t* sorted;               // the frame's splats in depth order
+  uint32_t* list;                       // LDS [kFwdRing]: ranks ahead of the batch, by position mod the ring's size
+  uint32_t* segs;                       // LDS [64]: the window's segments that have set bits
+  uint32_t SW, sh, nv, nseg, total;
+  uint32_t wseg = 0, wcnt = 0;          // next window: its first segment, this lane's segment's count
+  uint32_t nov = 0, kov = 0;            // segments with set bits in the window, and how many were read
+  uint32_t bits = 0, wrank = 0, winc = 0;   // this lane's word: bits not emitted, rank of bit 0, inclusive count
+  uint32_t wtot = 0, wdone = 0;         // (uniform) set bits of the 64 words held, and how many of them are emitted
+  uint32_t bend = 0;                    // (uniform) position after the emitted ones
+  uint32_t nbits = 0, nrank = 0;        // the next 64 words
+  bool nmore = false;                   // (uniform) there are any
+  int lane;
+
+  __device__ __forceinline__ RankStream(const PassArgs& a, int g, int b, uint32_t n, uint32_t* ring, uint32_t* sg,
+                                        int ln)
+      : row(a.tbits + (int64_t)g * a.bitmap_words), segc(a.seg_cnt + (int64_t)g * a.seg_stride), list(ring), segs(sg),
+        SW((uint32_t)a.seg_words), sh((uint32_t)__ffs(a.seg_words) - 1u), total(n), lane(ln) {
+    const uint32_t vbase = a.bkt_start[b * a.nbk];
+    nv = a.bkt_start[(b + 1) * a.nbk] - vbase;
+    sorted = a.depth_sorted + vbase;
+    nseg = ((nv + 31) / 32 + SW - 1) / SW;
+  }
+  __device__ __forceinline__ void start() {
+    wcnt = segc[min((uint32_t)lane, nseg - 1u)];
+    read_words();
+  }
+  // issues the load of the next 64 words
+  __device__ __forceinline__ void read_words() {
+    while (kov >= nov && wseg < nseg) {
+      const uint32_t sg = wseg + (uint32_t)lane;
+      const bool ne = sg < nseg && wcnt != 0u;
+      const unsigned long long om = __ballot(ne);
+      wave_sync();
+      if (ne) segs[lanes_below(om)] = sg;
+      wave_sync();
+      nov = (uint32_t)__popcll(om);
+      kov = 0;
+      wseg += 64u;
+      wcnt = segc[min(wseg + (uint32_t)lane, nseg - 1u)];
+    }
+    const uint32_t k = kov + ((uint32_t)lane >> sh);
+    const bool have = k < nov;
+    const uint32_t wq = have ? segs[k & 63u] * SW + ((uint32_t)lane & (SW - 1u)) : 0u;
+    const uint32_t w = row[wq];
+    nbits = have ? w : 0u;
+    nrank = wq * 32u;
+    nmore = kov < nov;
+    kov += 64u >> sh;
+  }
+  // the splats of positions [c0, c0 + 64) (lanes past the list's end: some splat of the frame)
+  __device__ __forceinline__ uint32_t read_splats(uint32_t c0) {
+    if (c0 >= total) return 0u;
+    const uint32_t c1 = min(c0 + (uint32_t)kFwdBatch, total);
+    while (bend < c1) {
+      if (wdone == wtot) {
+        if (!nmore) break;
+        bits = nbits;
+        wrank = nrank;
+        winc = wave_incl_scan(__popc(bits));
+        wtot = (uint32_t)__builtin_amdgcn_readlane((int)winc, 63);
+        wdone = 0;
+        read_words();
+      }
+      // the words that end within the ring (positions from c0 on are in use): all of them, but for dense rows
+      const int space = (int)(c0 + kFwdRing - bend);
+      const unsigned long long fit = __ballot((int)(winc - wdone) <= space);   // lane 0 on; never empty
+      const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)winc, 63 - __clzll((long long)fit));
+      if ((int)(winc - wdone) <= space) {
+        uint32_t at = bend + winc - wdone - __popc(bits);
+        while (bits != 0u) {
+          list[at & (kFwdRing - 1u)] = wrank + (uint32_t)__builtin_ctz(bits);
+          bits &= bits - 1u;
+          ++at;
+        }
+      }
+      bend += upto - wdone;
+      wdone = upto;
+    }
+    wave_sync();
+    const uint32_t rk = list[(c0 + (uint32_t)lane) & (kFwdRing - 1u)];
+    wave_sync();
+    return sorted[min(rk, nv - 1u)];   // (every rank is written)
+  }
+};
 
 template <int T>
 __global__ __launch_bounds__(64, T == 32 ? 1 : 6) void composite_fwd_kernel(PassArgs a, float* __restrict__ images) {
   using S = TileShape<T>;
   constexpr int NQ = S::NW;             // quadrants per tile
-  constexpr int U = 3;                  // entries evaluated together (independent alphas)
-  __shared__ StagedRec sr[kFwdBatch + 2 * U];   // the batch's candidates (one LDS address per entry)
+  constexpr int U = FwdGroup::N;        // entries evaluated together (independent alphas)
+  constexpr int kTook = 32 / U * U;     // entries whose takes a lane holds in a word
+  __shared__ FwdGroup sg[(kFwdBatch + U - 1) / U + 2];   // the batch's candidates
+  __shared__ uint32_t pos[kFwdBatch];       // and the position after each
   __shared__ uint32_t list[kFwdRing];       // ranks ahead of the batch, by position mod the ring's size
   __shared__ uint32_t segs[64];             // the window's segments that have set bits
   if (a.status->overflow) return;
@@ -733,114 +892,25 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 6) void composite_fwd_kernel(Pass
   const float qy0 = (float)(ty * T + S::qy(vt) * S::QW) + 0.5f;
   bool live = total > 0 && __ballot(mine) != 0ull;
 
-  // ---- the stream of ranks ----
-  const uint32_t* row = a.tbits + (int64_t)g * a.bitmap_words;
-  const uint16_t* segc = a.seg_cnt + (int64_t)g * a.seg_stride;
-  const uint32_t SW = (uint32_t)a.seg_words, sh = (uint32_t)__ffs(a.seg_words) - 1u;
-  const uint32_t vbase = a.bkt_start[b * a.nbk];
-  const uint32_t nv = a.bkt_start[(b + 1) * a.nbk] - vbase;
-  const uint32_t nseg = ((nv + 31) / 32 + SW - 1) / SW;
-  uint32_t wseg = 0, wcnt = 0;          // next window: its first segment, this lane's segment's count
-  uint32_t nov = 0, kov = 0;            // segments with set bits in the window, and how many were read
-  uint32_t bits = 0, wrank = 0, winc = 0;   // this lane's word: bits not emitted, rank of bit 0, inclusive count
-  uint32_t wtot = 0, wdone = 0;         // (uniform) set bits of the 64 words held, and how many of them are emitted
-  uint32_t bend = 0;                    // (uniform) position after the emitted ones
-  uint32_t nbits = 0, nrank = 0;        // the next 64 words
-  bool nmore = false;                   // (uniform) there are any
-  // issues the load of the next 64 words
-  auto read_words = [&]() {
-    while (kov >= nov && wseg < nseg) {
-      const uint32_t sg = wseg + (uint32_t)lane;
-      const bool ne = sg < nseg && wcnt != 0u;
-      const unsigned long long om = __ballot(ne);
-      wave_sync();
-      if (ne) segs[lanes_below(om)] = sg;
-      wave_sync();
-      nov = (uint32_t)__popcll(om);
-      kov = 0;
-      wseg += 64u;
-      wcnt = segc[min(wseg + (uint32_t)lane, nseg - 1u)];
-    }
-    const uint32_t k = kov + ((uint32_t)lane >> sh);
-    const bool have = k < nov;
-    const uint32_t wq = have ? segs[k & 63u] * SW + ((uint32_t)lane & (SW - 1u)) : 0u;
-    const uint32_t w = row[wq];
-    nbits = have ? w : 0u;
-    nrank = wq * 32u;
-    nmore = kov < nov;
-    kov += 64u >> sh;
-  };
-  // the splats of positions [c0, c0 + 64) (lanes past the list's end: some splat of the frame)
-  auto read_splats = [&](uint32_t c0) -> uint32_t {
-    if (c0 >= total) return 0u;
-    const uint32_t c1 = min(c0 + (uint32_t)kFwdBatch, total);
-    while (bend < c1) {
-      if (wdone == wtot) {
-        if (!nmore) break;
-        bits = nbits;
-        wrank = nrank;
-        winc = wave_incl_scan(__popc(bits));
-        wtot = (uint32_t)__builtin_amdgcn_readlane((int)winc, 63);
-        wdone = 0;
-        read_words();
-      }
-      // the words that end within the ring (positions from c0 on are in use): all of them, but for dense rows
-      const int space = (int)(c0 + kFwdRing - bend);
-      const unsigned long long fit = __ballot((int)(winc - wdone) <= space);   // lane 0 on; never empty
-      const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)winc, 63 - __clzll((long long)fit));
-      if ((int)(winc - wdone) <= space) {
-        uint32_t at = bend + winc - wdone - __popc(bits);
-        while (bits != 0u) {
-          list[at & (kFwdRing - 1u)] = wrank + (uint32_t)__builtin_ctz(bits);
-          bits &= bits - 1u;
-          ++at;
-        }
-      }
-      bend += upto - wdone;
-      wdone = upto;
-    }
-    wave_sync();
-    const uint32_t rk = list[(c0 + (uint32_t)lane) & (kFwdRing - 1u)];
-    wave_sync();
-    return a.depth_sorted[vbase + min(rk, nv - 1u)];   // (every rank is written)
-  };
+  RankStream stream(a, g, b, total, list, segs, lane);
   uint32_t sp0 = 0, sp1 = 0;            // splats of this batch and the next
   float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;   // this batch's records
   float qb = 0.f;
   if (live) {
-    wcnt = segc[min((uint32_t)lane, nseg - 1u)];
-    read_words();
-    sp0 = read_splats(0);
+    stream.start();
+    sp0 = stream.read_splats(0);
     const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)sp0 * kRecF);
     q0 = rec[0]; q1 = rec[1]; qb = rec[2].x;
-    sp1 = read_splats(kFwdBatch);
+    sp1 = stream.read_splats(kFwdBatch);
   }
   for (uint32_t c0 = 0; live && c0 < total; c0 += kFwdBatch) {
     const int n = (int)min((uint32_t)kFwdBatch, total - c0);
-    // ---- the rectangle of the pixel centres still running: lanes are 8 per
-    // row, so a column runs if any of its 8 lanes does, a row if its byte of
-    // the wave mask is nonzero ----
-    float sx0, sx1, sy0, sy1;
-    {
-      bool run = false;
+    // ---- the rectangle of the pixel centres still running ----
+    bool run = false;
 #pragma unroll
-      for (int p = 0; p < S::PX; ++p) run |= Te[p] > 0.0f;
-      const unsigned long long M = __ballot(run);
-      unsigned long long cm8 = M | (M >> 32);
-      cm8 |= cm8 >> 16;
-      cm8 |= cm8 >> 8;
-      cm8 &= 0xffull;
-      unsigned long long rm = M | (M >> 4);
-      rm |= rm >> 2;
-      rm |= rm >> 1;
-      rm &= 0x0101010101010101ull;
-      const int c0l = __ffsll((long long)cm8) - 1, c1l = 63 - __clzll((long long)cm8);
-      const int r0l = (__ffsll((long long)rm) - 1) >> 3, r1l = (63 - __clzll((long long)rm)) >> 3;
-      sx0 = qx0 + (float)(c0l * S::PXW);
-      sx1 = qx0 + (float)(c1l * S::PXW + S::PXW - 1);
-      sy0 = qy0 + (float)(r0l * S::PXW);
-      sy1 = qy0 + (float)(r1l * S::PXW + S::PXW - 1);
-    }
+    for (int p = 0; p < S::PX; ++p) run |= Te[p] > 0.0f;
+    float sx0, sx1, sy0, sy1;
+    running_rect<S::PXW>(__ballot(run), qx0, qy0, sx0, sx1, sy0, sy1);
     // ---- the batch's candidates compacted in list order ----
     if (lane < n) a.sorted[start + c0 + lane] = sp0;
     const bool cand = lane < n && strip_reach(q0, q1, sx0, sx1, sy0, sy1);
@@ -848,87 +918,72 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 6) void composite_fwd_kernel(Pass
     const int ncand = __popcll(cmk);      // (uniform)
     const int kslot = (int)lanes_below(cmk);   // this lane's candidate slot, if its entry is one
     if (cand) {
-      sr[kslot].r0 = q0;
-      sr[kslot].r1 = make_float2(q1.x, q1.y);
-      sr[kslot].c = make_float4(q1.z, q1.w, qb, __uint_as_float(c0 + (uint32_t)lane + 1u));
+      sg[kslot / U].put(kslot % U, q0, q1, qb);
+      pos[kslot] = c0 + (uint32_t)lane + 1u;
     }
-    if (lane < U) {                       // padding entries: opacity 0 (log2 -1e30), never taken; their colour 0
-      sr[ncand + lane].r1 = make_float2(0.f, -1e30f);   // (their mean and conic may be anything:
-      sr[ncand + lane].c = make_float4(0.f, 0.f, 0.f, 0.f);   // min(power, -1e30) = -1e30)
-    }
+    // padding entries: opacity 0 (log2 -1e30), never taken; their colour 0
+    // (the mean and conic may be anything: min(power, -1e30) = -1e30)
+    if (lane < U) sg[(ncand + lane) / U].pad((ncand + lane) % U);
     wave_sync();
     // ---- the batches behind this one: records of the first, indices of the second ----
     const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)sp1 * kRecF);
     q0 = rec[0]; q1 = rec[1]; qb = rec[2].x;
     sp0 = sp1;
-    sp1 = read_splats(c0 + 2 * kFwdBatch);
+    sp1 = stream.read_splats(c0 + 2 * kFwdBatch);
     // ---- compositing: the candidates in list order, U at a time; a group's
     // conics are read while the group before it is blended, its colours while
     // its alphas are formed ----
-    unsigned long long tookm = 0ull;      // (uniform) bit 63 - k: some pixel took candidate k
-    float4 r0[U];
-    float2 r1[U];
+    unsigned long long tookm = 0ull;      // (uniform) bit k: some pixel took candidate k
+    float4 r0[U], r1a = sg[0].v[U], r1b = sg[0].v[U + 1];
 #pragma unroll
-    for (int u = 0; u < U; ++u) { r0[u] = sr[u].r0; r1[u] = sr[u].r1; }
-    for (int k = 0; k < ncand; k += U) {
-      float4 col[U];
+    for (int u = 0; u < U; ++u) r0[u] = sg[0].v[u];
+    const FwdGroup* grp = sg;
+    for (int k0 = 0; live && k0 < ncand; k0 += kTook) {
+      const int k1 = min(ncand, k0 + kTook);
+      uint32_t took[S::PX];               // bit k - 1 - j: the pixel took candidate j of [k0, k)
 #pragma unroll
-      for (int u = 0; u < U; ++u) col[u] = sr[k + u].c;
-      float al[S::PX][U];
+      for (int p = 0; p < S::PX; ++p) took[p] = 0u;
+      int k = k0;
+      do {
+        const float4 ca = grp->v[U + 2], cb = grp->v[U + 3], cd = grp->v[U + 4];
+        const float cr[U] = {ca.x, ca.w, cb.z, cd.y}, cg[U] = {ca.y, cb.x, cb.w, cd.z}, cl[U] = {ca.z, cb.y, cd.x, cd.w};
+        const float cc[U] = {r1a.x, r1a.z, r1b.x, r1b.z}, lo[U] = {r1a.y, r1a.w, r1b.y, r1b.w};
+        float al[S::PX][U];
 #pragma unroll
-      for (int p = 0; p < S::PX; ++p)
+        for (int p = 0; p < S::PX; ++p)
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float dx, dy, pwr;
-          al[p][u] = splat_alpha(r0[u], r1[u].x, r1[u].y, pxf[p], pyf[p], dx, dy, pwr);
+          for (int u = 0; u < U; ++u) al[p][u] = clamped_alpha(r0[u], cc[u], lo[u], pxf[p], pyf[p]);
+        __builtin_amdgcn_sched_barrier(0);
+        ++grp;
+#pragma unroll
+        for (int u = 0; u < U; ++u) r0[u] = grp->v[u];
+        r1a = grp->v[U];
+        r1b = grp->v[U + 1];
+        k += U;
+        bool run = false;
+#pragma unroll
+        for (int p = 0; p < S::PX; ++p) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const float nw = fold_step(al[p][u] >= kAlphaMin ? al[p][u] : -0.0f, Te[p], took[p]);
+            C0[p] = __builtin_fmaf(-nw, cr[u], C0[p]);
+            C1[p] = __builtin_fmaf(-nw, cg[u], C1[p]);
+            C2[p] = __builtin_fmaf(-nw, cl[u], C2[p]);
+          }
+          run |= Te[p] > 0.0f;
         }
-#pragma unroll
-      for (int u = 0; u < U; ++u) { r0[u] = sr[k + U + u].r0; r1[u] = sr[k + U + u].r1; }
-      // (each position is read with its colour: the compiler would sink it
-      // into a branch on the lanes that take the entry)
-#pragma unroll
-      for (int u = 0; u < U; ++u) asm("" : "+v"(col[u].w));
-      unsigned long long tm[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) tm[u] = 0ull;
+        live = __builtin_amdgcn_ballot_w64(run) != 0ull;
+      } while (k < (live ? k1 : 0));
+      uint32_t any = 0u;
 #pragma unroll
       for (int p = 0; p < S::PX; ++p) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          // the front-to-back step: alpha below 1/255 is skipped (w = 0, Te
-          // passes unchanged), T (1 - alpha) < 1e-4 stops the pixel before
-          // this entry (Te -> -T); a stopped pixel has Te <= 0, so its tn <= 0
-          // stops it again (Te kept: -|Te|) and it takes nothing
-          const float w = (al[p][u] >= kAlphaMin) ? fminf(al[p][u], kAlphaMax) : 0.0f;
-          const float tn = __builtin_fmaf(-w, Te[p], Te[p]);   // T (1 - alpha), rounded once
-          const bool stop = tn < kTMin;
-          const float wgt = stop ? 0.0f : w * Te[p];
-          C0[p] = __builtin_fmaf(wgt, col[u].x, C0[p]);
-          C1[p] = __builtin_fmaf(wgt, col[u].y, C1[p]);
-          C2[p] = __builtin_fmaf(wgt, col[u].z, C2[p]);
-          Te[p] = stop ? -fabsf(Te[p]) : tn;   // one select with source modifiers
-          const bool take = wgt > 0.0f;   // w >= 1/255 and Te >= 1e-4: never 0 when taken
-          last[p] = take ? __float_as_uint(col[u].w) : last[p];
-          tm[u] |= __builtin_amdgcn_ballot_w64(take);
-        }
+        if (took[p] != 0u) last[p] = pos[k - 1 - __builtin_ctz(took[p])];
+        any |= took[p];
       }
-      // bit U - 1 - u: some pixel took candidate k + u; each mask shifted in
-      // on the scalar unit (the compiler builds it with vector ORs)
-      uint32_t m4 = 0u;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        asm("s_cmp_lg_u64 %1, 0\n\ts_addc_u32 %0, %0, %0" : "+s"(m4) : "s"(tm[u]) : "scc");
-      tookm |= ((unsigned long long)m4 << (64 - U)) >> k;   // bit 63 - k: candidate k
-      bool mine_now = false;
-#pragma unroll
-      for (int p = 0; p < S::PX; ++p) mine_now |= Te[p] > 0.0f;
-      if (__builtin_amdgcn_ballot_w64(mine_now) == 0ull) {
-        live = false;
-        break;
-      }
+      tookm |= (unsigned long long)(__builtin_bitreverse32(wave_or(any)) >> (32 - (k - k0))) << k0;
     }
     // the entries of the batch that the quadrant took
-    const unsigned long long taken = __ballot(cand && ((tookm >> (63 - kslot)) & 1ull));
+    const unsigned long long taken = __ballot(cand && ((tookm >> kslot) & 1ull));
     if (lane == 0) a.qmask[4 * ((int64_t)(start >> 6) + g + (c0 >> 6)) + q] = taken;
     wave_sync();                          // the candidates' slots are rewritten by the next batch
   }
