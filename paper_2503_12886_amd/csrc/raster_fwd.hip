@@ -1008,10 +1008,249 @@ __global__ __launch_bounds__(64, T == 32 ? 1 : 6) void composite_fwd_kernel(Pass
   if (lane < 4 && (lane == q || NQ == 1)) a.qlast[g * 4 + lane] = lane == q ? my_last : 0u;
 }
 
+// The same for few tiles (launch_composite_fwd), a workgroup of three waves to
+// each quadrant: a lone wave issues an instruction every four cycles or so,
+// whatever it is, and the longest list's instructions are the pass's time; the
+// chip has room for more waves, so a quadrant's walk is made a pipeline of
+// three parts, near enough equal for a batch of 20 candidates.  One wave reads the list and stages a batch's
+// candidates, at most kStepMax of them a step; one forms the alphas of the
+// step before at the quadrant's pixels, to LDS; one folds those of the step
+// before that.  A barrier ends a step.  The entries are culled against the
+// pixels that ran two steps earlier: no fewer than run now, so only entries
+// that nothing takes are added.  Every alpha and every fold is the one-wave
+// kernel's operation on the same values.
+//
+// One 512 x 512 frame of 50k Gaussians 78 -> 57 us, of 200k 169 -> 107, one
+// 128 x 128 frame of 2k 35 -> 29.  With at most 16 or 24 candidates a step
+// (less LDS, more workgroups in flight): 62, 61 for the first.
+constexpr int kStepMax = 32;
+
+struct FwdStep {
+  unsigned long long cand;              // the batch's candidates
+  uint32_t c0;                          // the batch's first position
+  uint32_t n;                           // candidates of this step
+  uint32_t first;                       // the batch's candidates before them
+  uint32_t ends;                        // bit 0: the batch ends with this step, bit 1: the list does
+};
+
+// a value that all lanes hold, to the scalar unit
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ unsigned long long uniform(unsigned long long x) {
+  return (unsigned long long)uniform((uint32_t)(x >> 32)) << 32 | uniform((uint32_t)x);
+}
+
+template <int T>
+__global__ __launch_bounds__(192) void composite_fwd_split_kernel(PassArgs a, float* __restrict__ images) {
+  using S = TileShape<T>;
+  static_assert(S::PX == 1, "a pixel to a lane");
+  constexpr int NQ = S::NW;
+  constexpr int U = FwdGroup::N;        // entries taken together
+  __shared__ FwdGroup sg[3][kStepMax / U + 1];
+  __shared__ uint32_t pos[3][kStepMax];
+  __shared__ float alpha[(2 * kStepMax + U) * 64];   // two steps' (and what is read past the second)
+  __shared__ FwdStep info[3];
+  __shared__ unsigned long long running[2];
+  __shared__ uint32_t list[kFwdRing];
+  __shared__ uint32_t segs[64];
+  if (a.status->overflow) return;
+  const int lane = threadIdx.x & 63, role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int r = blockIdx.x, q = 0;
+  if (NQ > 1) {
+    const int grp = blockIdx.x / (8 * NQ), within = blockIdx.x % (8 * NQ);
+    q = within / 8;
+    r = grp * 8 + within % 8;
+  }
+  const int g = tile_of_rank(a.cls_cnt, a.order_fwd, a.n_tiles, r);
+  if (g < 0) return;
+  const int b = frame_of_tile(a.frames, a.B, g);
+  const FrameDev& F = a.frames[b];
+  const int lt = g - F.tile_base;
+  const int tx = lt % F.ntx, ty = lt / F.ntx;
+  const uint32_t start = a.tile_start[g], total = a.tile_start[g + 1] - start;
+  const int vt = q * 64 + lane;
+  const int px = tx * T + S::lx0(vt), py = ty * T + S::ly0(vt);
+  const float pxf = (float)px + 0.5f, pyf = (float)py + 0.5f;
+  const bool inside = px < F.W && py < F.H;
+  const unsigned long long all = __ballot(inside);
+  float Te = inside ? 1.0f : 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;   // (the fold's)
+  uint32_t last = 0;
+  if (total > 0 && all != 0ull) {       // (uniform over the workgroup)
+    if (threadIdx.x < 3) info[threadIdx.x] = FwdStep{0ull, 0u, 0u, 0u, 0u};
+    if (threadIdx.x < 2) running[threadIdx.x] = all;
+    __syncthreads();
+    int st = 0;                         // step mod 3
+    if (role == 2) {
+      RankStream stream(a, g, b, total, list, segs, lane);
+      stream.start();
+      const float qx0 = (float)(tx * T + S::qx(vt) * S::QW) + 0.5f;
+      const float qy0 = (float)(ty * T + S::qy(vt) * S::QW) + 0.5f;
+      uint32_t c0 = 0, i = 0;           // this batch, this step
+      unsigned long long M = all;
+      // splats of this batch and the two behind it
+      uint32_t sp0 = stream.read_splats(0), sp1 = stream.read_splats(kFwdBatch);
+      uint32_t sp2 = stream.read_splats(2 * kFwdBatch);
+      auto record = [&](uint32_t sp, float4& q0, float4& q1, float& qb) {
+        const float4* rec = reinterpret_cast<const float4*>(a.rec + (int64_t)sp * kRecF);
+        q0 = rec[0]; q1 = rec[1]; qb = rec[2].x;
+      };
+      // the steps of a batch whose records are q; q is left with those of the
+      // batch after the next, so that every load has a step or more to arrive.
+      // Returns whether the pipeline has ended.
+      auto batch = [&](float4& q0, float4& q1, float& qb) -> bool {
+        unsigned long long cmk = 0ull;
+        if (c0 < total) {
+          const int n = (int)min((uint32_t)kFwdBatch, total - c0);
+          float sx0, sx1, sy0, sy1;
+          running_rect<1>(M, qx0, qy0, sx0, sx1, sy0, sy1);
+          if (lane < n) a.sorted[start + c0 + lane] = sp0;
+          cmk = __ballot(lane < n && strip_reach(q0, q1, sx0, sx1, sy0, sy1));
+        }
+        const uint32_t ncand = (uint32_t)__popcll(cmk), kslot = lanes_below(cmk);
+        const bool cand = (cmk >> lane) & 1ull;
+        for (uint32_t done = 0;; done += kStepMax) {
+          const uint32_t nst = min(ncand - done, (uint32_t)kStepMax);
+          const bool whole = done + nst == ncand;
+          const uint32_t k = kslot - done;
+          if (cand && k < nst) {
+            sg[st][k / U].put(k % U, q0, q1, qb);
+            pos[st][k] = c0 + (uint32_t)lane + 1u;
+          }
+          if (lane < U) sg[st][(nst + lane) / U].pad((nst + lane) % U);
+          if (lane == 0)
+            info[st] = FwdStep{cmk, c0, nst, done,
+                               c0 < total && whole ? 1u | (c0 + kFwdBatch >= total ? 2u : 0u) : 0u};
+          if (whole) {
+            sp0 = sp1;
+            const uint32_t sp = sp2;
+            sp1 = sp2;
+            sp2 = stream.read_splats(c0 + 3 * kFwdBatch);
+            record(sp, q0, q1, qb);
+            c0 += c0 < total ? kFwdBatch : 0u;
+          }
+          st = st == 2 ? 0 : st + 1;
+          __syncthreads();
+          M = uniform(running[i++ & 1u]);
+          if (M == 0ull) return true;
+          if (whole) return false;
+        }
+      };
+      float4 qa0, qa1, qb0, qb1;
+      float qa2, qb2;
+      record(sp0, qa0, qa1, qa2);
+      record(sp1, qb0, qb1, qb2);
+      while (!batch(qa0, qa1, qa2) && !batch(qb0, qb1, qb2)) {
+      }
+    } else if (role == 1) {
+      st = 2;
+      for (uint32_t i = 0;; ++i) {
+        const int n = uniform(info[st].n);
+        const FwdGroup* in = sg[st];
+        float* out = alpha + (i & 1u) * (kStepMax * 64) + lane;
+        float4 r0[U], r1a = in->v[U], r1b = in->v[U + 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r0[u] = in->v[u];
+        for (int k = 0; k < n; k += U) {
+          const float cc[U] = {r1a.x, r1a.z, r1b.x, r1b.z}, lo[U] = {r1a.y, r1a.w, r1b.y, r1b.w};
+          float al[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) al[u] = clamped_alpha(r0[u], cc[u], lo[u], pxf, pyf);
+          __builtin_amdgcn_sched_barrier(0);
+          ++in;
+#pragma unroll
+          for (int u = 0; u < U; ++u) r0[u] = in->v[u];
+          r1a = in->v[U];
+          r1b = in->v[U + 1];
+#pragma unroll
+          for (int u = 0; u < U; ++u) out[(k + u) * 64] = (al[u] >= kAlphaMin) ? al[u] : -0.0f;
+        }
+        st = st == 2 ? 0 : st + 1;
+        __syncthreads();
+        if (uniform(running[i & 1u]) == 0ull) break;
+      }
+    } else {
+      st = 1;
+      unsigned long long tookm = 0ull;  // bit k: some pixel took the batch's candidate k
+      for (uint32_t i = 0;; ++i) {
+        const int n = uniform(info[st].n);
+        const uint32_t first = uniform(info[st].first), ends = uniform(info[st].ends);
+        const FwdGroup* in = sg[st];
+        const float* w = alpha + (~i & 1u) * (kStepMax * 64) + lane;
+        unsigned long long M = __ballot(Te > 0.0f);
+        uint32_t took = 0u;             // bit k - 1 - j: the pixel took the step's candidate j
+        int k = 0;
+        float wu[U];
+        float4 ca = in->v[U + 2], cb = in->v[U + 3], cd = in->v[U + 4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) wu[u] = w[u * 64];
+        while (k < n && M != 0ull) {
+          const float cr[U] = {ca.x, ca.w, cb.z, cd.y}, cg[U] = {ca.y, cb.x, cb.w, cd.z}, cl[U] = {ca.z, cb.y, cd.x, cd.w};
+          float nw[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) nw[u] = fold_step(wu[u], Te, took);
+          k += U;
+          w += U * 64;
+#pragma unroll
+          for (int u = 0; u < U; ++u) wu[u] = w[u * 64];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            C0 = __builtin_fmaf(-nw[u], cr[u], C0);
+            C1 = __builtin_fmaf(-nw[u], cg[u], C1);
+            C2 = __builtin_fmaf(-nw[u], cl[u], C2);
+          }
+          ++in;
+          ca = in->v[U + 2]; cb = in->v[U + 3]; cd = in->v[U + 4];
+          M = __builtin_amdgcn_ballot_w64(Te > 0.0f);
+        }
+        if (k > 0) {
+          if (took != 0u) last = pos[st][k - 1 - __builtin_ctz(took)];
+          tookm |= (unsigned long long)(__builtin_bitreverse32(wave_or(took)) >> (32 - k)) << first;
+        }
+        if ((ends & 1u) || (M == 0ull && n > 0)) {
+          const unsigned long long cmk = info[st].cand;
+          const int kslot = (int)lanes_below(cmk);
+          const unsigned long long taken = __ballot(((cmk >> lane) & 1ull) && ((tookm >> kslot) & 1ull));
+          if (lane == 0) a.qmask[4 * ((int64_t)(start >> 6) + g + (info[st].c0 >> 6)) + q] = taken;
+          tookm = 0ull;
+        }
+        if (lane == 0) running[i & 1u] = (ends & 2u) ? 0ull : M;
+        st = st == 2 ? 0 : st + 1;
+        __syncthreads();
+        if (uniform(running[i & 1u]) == 0ull) break;
+      }
+    }
+  }
+  if (role != 0) return;
+  if (inside) {
+    const int64_t pix = (int64_t)py * F.W + px;
+    const int64_t hw = (int64_t)F.W * F.H;
+    float* img = images + F.pix_base * 3;
+    const float Tfin = fabsf(Te);
+    img[pix] = C0 + Tfin * F.bg[0];
+    img[hw + pix] = C1 + Tfin * F.bg[1];
+    img[2 * hw + pix] = C2 + Tfin * F.bg[2];
+    a.n_iter[F.pix_base + pix] = last;
+    a.t_final[F.pix_base + pix] = Tfin;
+  }
+  last = wave_max_u32(last);
+  if (lane < 4 && (lane == q || NQ == 1)) a.qlast[g * 4 + lane] = lane == q ? last : 0u;
+}
+
+constexpr int kSplitTiles = 1280;
+
 void launch_composite_fwd(const PassArgs& a, float* images, hipStream_t s) {
   if (a.n_tiles == 0) return;
   const int nq = a.tile == 8 ? 1 : 4;
   const dim3 grid(nq == 1 ? a.n_tiles : div_up(a.n_tiles, 8) * 8 * nq);
+  // Past some 1300 tiles the chip is full of waves and the pipeline's barriers
+  // and LDS traffic cost more than its shorter chains save; below 8 splats a
+  // tile there is no chain to shorten.  One wave / three waves (us): 50k splats
+  // on 1024 tiles 74 / 51, on 1536 65 / 65, on 2048 79 / 68 but 20k 48 / 56,
+  // 150k on 3072 85 / 100, 60k on 1250 58 / 49; on 1024 tiles 10k 33 / 30,
+  // 5k 24 / 26, 4k 30 / 30.
+  if (a.tile == 16 && a.n_tiles <= kSplitTiles && a.n_splats >= 8 * (int64_t)a.n_tiles) {
+    hipLaunchKernelGGL(composite_fwd_split_kernel<16>, grid, dim3(192), 0, s, a, images);
+    return;
+  }
   if (a.tile == 8) hipLaunchKernelGGL(composite_fwd_kernel<8>, grid, dim3(64), 0, s, a, images);
   else if (a.tile == 16) hipLaunchKernelGGL(composite_fwd_kernel<16>, grid, dim3(64), 0, s, a, images);
   else hipLaunchKernelGGL(composite_fwd_kernel<32>, grid, dim3(64), 0, s, a, images);
