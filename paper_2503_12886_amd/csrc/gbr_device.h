@@ -45,6 +45,24 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// min(alpha, 0.99) of a splat at a pixel, bit-identical in the forward and the
+// backward pass: power = ca dx^2 + cb dx dy + cc dy^2 (r0.z, r0.w, cc) plus
+// lo = log2 opacity, clamped at lo, and alpha = 2^power.  v_exp_f32 gives 0.99f itself at kAlphaMaxLog2
+// (and some 45 float32 to either side), no more below and no less above, so the
+// clamp goes to the power, where it is an operand of the minimum that is
+// taken anyway.
+constexpr float kAlphaMaxLog2 = -0.014499555f;
+__device__ __forceinline__ float clamped_alpha(float4 r0, float cc, float lo, float px, float py) {
+#pragma clang fp contract(off)
+  const float dx = px - r0.x, dy = py - r0.y;
+  float pw = __builtin_fmaf(r0.z * dx, dx, lo);
+  pw = __builtin_fmaf(r0.w * dx, dy, pw);
+  pw = __builtin_fmaf(cc * dy, dy, pw);
+  float pc;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(pc) : "v"(pw), "v"(lo), "s"(kAlphaMaxLog2));
+  return __builtin_amdgcn_exp2f(pc);
+}
+
 // Exclusive scan of one value per thread across a block of NT threads.
 template <int NT>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* lds_waves, uint32_t* total) {

@@ -325,36 +325,42 @@ __global__ __launch_bounds__(TileShapeB<32>::NT) void composite_bwd32_kernel(Pas
 // bytes per entry, records read between two barriers): 16 frames of 512 x 512
 // and 50k Gaussians 402 -> 302, 10 mesh-bound ones 638 -> 405, 64 uneven
 // frames of 100k 1285 -> 1080, five of 333 x 500 166 -> 117, one of 128 x 128
-// 88 -> 56.  Bound by instruction issue: 144M vector operations (204M before),
-// 80 % of the slots, 5 waves a SIMD by LDS.
-constexpr int kBwdRow = 68;               // floats per LDS row of 64 pixels: rows 4 banks apart
+// 88 -> 56.  With alpha / (1 - alpha) in place of 1 / (1 - alpha), the clamp
+// in the power, and the rows' reads contiguous (below): 304 -> 294, 404 -> 391,
+// 1090 -> 1065, 118 -> 114, 56 -> 54.  Bound by instruction issue: 140M vector
+// operations (204M at first), 80 % of the slots, 5 waves a SIMD by LDS.
+// A row of 64 pixels in LDS: the halves of the quadrant's rows (4 pixels, 16
+// bytes) in order of (half, row), so that the 8 lanes of an entry read 128
+// bytes in one piece.  The bank conflicts that are left (a quarter of the LDS
+// cycles: rows a multiple of the banks apart, the lower half of a write's lanes
+// in 16 banks) cost nothing: without any of them 294 as well.
+constexpr int kBwdRow = 64;
 
 // One entry folded into a lane's back-to-front state (transmittance in front
 // of the entry, colour behind it), in two parts.  A lane whose pixel did not
-// take the entry folds alpha 0: 1 / (1 - 0) = 1 exactly, so its state passes
-// through unchanged and t and the weight are 0.  (Where rounding makes the
+// take the entry folds alpha / (1 - alpha) = 0: its state passes through
+// unchanged and t and the weight are 0.  (Where rounding makes the
 // clamped quadratic form negative, at a pixel on the mean, the power's
 // gradient passes as it does without the rounding.)
 struct EntryAlpha {
-  float al, inv, cg;     // alpha, 1 / (1 - alpha), <colour, dL/dout>
+  float q, cg;           // alpha / (1 - alpha), <colour, dL/dout>
   bool below;            // not clamped
 };
-__device__ __forceinline__ EntryAlpha entry_alpha(float a0, bool before_stop, const float4 r1, float cbl, float G0,
+__device__ __forceinline__ EntryAlpha entry_alpha(float al, bool before_stop, const float4 r1, float cbl, float G0,
                                                   float G1, float G2) {
   EntryAlpha x;
-  x.al = before_stop && a0 >= kAlphaMin ? fminf(a0, kAlphaMax) : 0.0f;
-  x.inv = __builtin_amdgcn_rcpf(1.0f - x.al);
+  const float q = al * __builtin_amdgcn_rcpf(1.0f - al);
+  x.q = before_stop && al >= kAlphaMin ? q : 0.0f;
   x.cg = r1.z * G0 + r1.w * G1 + cbl * G2;
-  x.below = a0 < kAlphaMax;                         // min(0.99, .) passes the gradient only below the clamp
+  x.below = al < kAlphaMax;                         // min(0.99, .) passes the gradient only below the clamp
   return x;
 }
 __device__ __forceinline__ void entry_fold(const EntryAlpha& x, float& T_, float& SG, float& t, float& wgt) {
-  const float Ti = T_ * x.inv;                      // transmittance in front of this entry
-  wgt = x.al * Ti;
-  const float dal = Ti * x.cg - SG * x.inv;         // d out / d alpha
+  const float d = T_ * x.cg - SG;                   // (1 - alpha) d out / d alpha
+  wgt = x.q * T_;                                   // alpha times the transmittance in front of the entry
   SG += wgt * x.cg;                                 // <colour behind, dL/dout>
-  T_ = Ti;
-  t = x.below ? x.al * dal : 0.0f;
+  T_ += wgt;
+  t = x.below ? x.q * d : 0.0f;
 }
 
 // The highest set bit of a wave-uniform mask, cleared there (64: none).
@@ -427,17 +433,18 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
   // lane / 8 of a group; the image gradients of that row's pixels
   const float oy = (float)(lane & 7) - 3.5f;
   float* tw = tb[w];
-  const float* twr = tw + (lane >> 3) * kBwdRow + (lane & 7) * 8;
+  const float* twr = tw + (lane >> 3) * kBwdRow + (lane & 7) * 4;
+  const int cell = (lane & 4) * 8 + (lane >> 3) * 4 + (lane & 3);
   const int value = 4 * (lane & 1) + (lane & 2) + ((lane >> 2) & 1);   // which of the sums the lane ends with
   float gx[8][3];
   if (threadIdx.x < 3) st[threadIdx.x][64] = make_float4(0.0f, threadIdx.x == 1 ? -1e30f : 0.0f, 0.0f, 0.0f);
   {
-    tw[lane] = G0; tw[kBwdRow + lane] = G1; tw[2 * kBwdRow + lane] = G2;
+    tw[cell] = G0; tw[kBwdRow + cell] = G1; tw[2 * kBwdRow + cell] = G2;
     wave_sync();
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
-      for (int k = 0; k < 8; ++k) gx[k][c] = tw[c * kBwdRow + (lane & 7) * 8 + k];
+      for (int k = 0; k < 8; ++k) gx[k][c] = tw[c * kBwdRow + (k & 4) * 8 + (lane & 7) * 4 + (k & 3)];
     wave_sync();
   }
   // this lane's part of a batch's write-out: a quadrant's sums of one entry
@@ -501,17 +508,17 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
           eh = (h & 1) ? (eh & 0xffffu) | (pair << 16) : 0x40400000u | pair;
           const float4 a0 = st[0][ea], a1 = st[1][ea], b0 = st[0][eb], b1 = st[1][eb];
           const float a2 = st[2][ea].x, b2 = st[2][eb].x;
-          float dx, dy, pwr, ta, wa, tc, wc;
-          const float aa = splat_alpha_b(a0, a1, pxf, pyf, dx, dy, pwr);
-          const float ab = splat_alpha_b(b0, b1, pxf, pyf, dx, dy, pwr);
+          float ta, wa, tc, wc;
+          const float aa = clamped_alpha(a0, a1.x, a1.y, pxf, pyf);
+          const float ab = clamped_alpha(b0, b1.x, b1.y, pxf, pyf);
           const EntryAlpha xa = entry_alpha(aa, c0 + ea < nit, a1, a2, G0, G1, G2);
           const EntryAlpha xb = entry_alpha(ab, c0 + eb < nit, b1, b2, G0, G1, G2);
           entry_fold(xa, T_, SG, ta, wa);
           entry_fold(xb, T_, SG, tc, wc);
-          tw[(2 * h) * kBwdRow + lane] = ta;
-          tw[(2 * h + 1) * kBwdRow + lane] = tc;
-          tw[(8 + 2 * h) * kBwdRow + lane] = wa;
-          tw[(9 + 2 * h) * kBwdRow + lane] = wc;
+          tw[(2 * h) * kBwdRow + cell] = ta;
+          tw[(2 * h + 1) * kBwdRow + cell] = tc;
+          tw[(8 + 2 * h) * kBwdRow + cell] = wa;
+          tw[(9 + 2 * h) * kBwdRow + cell] = wc;
         }
       }
       wave_sync();
@@ -519,8 +526,9 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
       float t[8], wg[8];
 #pragma unroll
       for (int k = 0; k < 8; k += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(twr + k);
-        const float4 y = *reinterpret_cast<const float4*>(twr + 8 * kBwdRow + k);
+        float4 x = *reinterpret_cast<const float4*>(twr + 8 * k);
+        float4 y = *reinterpret_cast<const float4*>(twr + 8 * kBwdRow + 8 * k);
+        asm("" : "+v"(x.x), "+v"(x.y), "+v"(x.z), "+v"(x.w));   // (as one read of 16 bytes)
         t[k] = x.x; t[k + 1] = x.y; t[k + 2] = x.z; t[k + 3] = x.w;
         wg[k] = y.x; wg[k + 1] = y.y; wg[k + 2] = y.z; wg[k + 3] = y.w;
       }

@@ -657,22 +657,6 @@ __device__ __forceinline__ float splat_alpha(float4 r0, float cc, float lo, floa
   return __builtin_amdgcn_exp2f(pc);
 }
 
-// min(alpha, 0.99) of the same.  v_exp_f32 gives 0.99f itself at kAlphaMaxLog2
-// (and some 45 float32 to either side), no more below and no less above, so the
-// clamp goes to the power, where it is an operand of the minimum that is
-// taken anyway.
-constexpr float kAlphaMaxLog2 = -0.014499555f;
-__device__ __forceinline__ float clamped_alpha(float4 r0, float cc, float lo, float px, float py) {
-#pragma clang fp contract(off)
-  const float dx = px - r0.x, dy = py - r0.y;
-  float pw = __builtin_fmaf(r0.z * dx, dx, lo);
-  pw = __builtin_fmaf(r0.w * dx, dy, pw);
-  pw = __builtin_fmaf(cc * dy, dy, pw);
-  float pc;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(pc) : "v"(pw), "v"(lo), "s"(kAlphaMaxLog2));
-  return __builtin_amdgcn_exp2f(pc);
-}
-
 // The front-to-back step of an entry at a pixel: w is its alpha, or -0 where
 // that is below 1/255 (the entry is skipped, Te passes unchanged).
 // T (1 - alpha) < 1e-4 stops the pixel before this entry (Te -> -T); a stopped
