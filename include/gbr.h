@@ -276,6 +276,23 @@ int gbr_loss(gbr_ctx* ctx, const float* images, const float* targets, int32_t ki
    Limits: d_in <= 1024, hidden <= 1024, K <= 64. */
 int gbr_mlp_forward(gbr_ctx* ctx, const float* params, const float* theta, int32_t B, int32_t d_in, int32_t hidden,
                     int32_t K, float* psi, void* stream);
+/* gbr_mlp_forward and gbr_blend of several models, each with frames and
+   Gaussians of its own, in two launches (per 16 models): psi [B][K] = F(theta
+   [B][d_in]), raw [B][N][16] blended from bases [(K+1)][N][16], with the bits
+   of the two calls.  Keeps no activations.  1 <= K <= 63, else the limits of
+   both; the groups' psi and raw must not overlap. */
+typedef struct {
+  const float* mlp;
+  const float* theta;
+  const float* bases;
+  float* psi;
+  float* raw;
+  int64_t N;
+  int32_t B;
+  int32_t K;
+} gbr_drive_group;
+int gbr_drive(gbr_ctx* ctx, int32_t n_groups, const gbr_drive_group* groups, int32_t d_in, int32_t hidden,
+              void* stream);
 /* dpsi [B][K] -> dparams (same packing as params, overwritten). */
 int gbr_mlp_backward(gbr_ctx* ctx, const float* params, const float* dpsi, float* dparams, void* stream);
 

@@ -57,11 +57,9 @@ __global__ void blend_weights_f64_kernel(const float* __restrict__ weights, int 
 }
 
 template <int KM>   // KM >= K + 1: slice values kept in registers
-__global__ __launch_bounds__(kBlendThreads) void blend_fwd_kernel(const float* __restrict__ bases,
-                                                                   const double* __restrict__ w64, int B, int K,
-                                                                   int64_t N, float* __restrict__ raw) {
+__device__ __forceinline__ void blend_element(const float* __restrict__ bases, const double* __restrict__ w64, int B,
+                                              int K, int64_t N, int64_t i, float* __restrict__ raw) {
   const int64_t L = N * kNF;
-  const int64_t i = (int64_t)blockIdx.x * kBlendThreads + threadIdx.x;
   if (i >= L) return;
   const bool pad = (i % kNF) >= 14;
   // every load is issued unconditionally (slice index clamped into range) so
@@ -79,6 +77,32 @@ __global__ __launch_bounds__(kBlendThreads) void blend_fwd_kernel(const float* _
     for (int k = 1; k < KM; ++k) acc = __builtin_fma(w[k], v[k], acc);   // exact product, one rounding per step
     raw[(int64_t)b * L + i] = pad ? 0.0f : (float)acc;
   }
+}
+
+template <int KM>
+__global__ __launch_bounds__(kBlendThreads) void blend_fwd_kernel(const float* __restrict__ bases,
+                                                                   const double* __restrict__ w64, int B, int K,
+                                                                   int64_t N, float* __restrict__ raw) {
+  blend_element<KM>(bases, w64, B, K, N, (int64_t)blockIdx.x * kBlendThreads + threadIdx.x, raw);
+}
+
+// The blends of several models in one launch (gbr_drive), so that one fills
+// the chip where the last one's workgroups run out: 8 models of 20k to 100k
+// Gaussians and 21 slices, 146 us in eight launches -> 123.
+template <int KM>
+__global__ __launch_bounds__(kBlendThreads) void blend_drive_kernel(DriveTable t) {
+  const int gi = t.group_of(t.block0, blockIdx.x);
+  const DriveGroup& g = t.g[gi];
+  blend_element<KM>(g.bases, t.w64 + (int64_t)t.frame0[gi] * kBlendW64Stride, g.B, g.K, g.N,
+                    (int64_t)(blockIdx.x - t.block0[gi]) * kBlendThreads + threadIdx.x, g.raw);
+}
+
+int64_t blend_drive_blocks(int64_t N) { return div_up(N * kNF, kBlendThreads); }
+
+void launch_blend_drive(const DriveTable& t, int max_K, hipStream_t s) {
+  with_slices(max_K, [&](auto km) {
+    hipLaunchKernelGGL(blend_drive_kernel<km()>, dim3(t.blocks), dim3(kBlendThreads), 0, s, t);
+  });
 }
 
 void launch_blend_fwd(const float* bases, const float* weights, int B, int K, int64_t N, float* raw, double* w64,

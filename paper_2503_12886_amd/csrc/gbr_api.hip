@@ -970,6 +970,54 @@ int gbr_mlp_forward(gbr_ctx* c, const float* params, const float* theta, int32_t
   return GBR_OK;
 }
 
+int gbr_drive(gbr_ctx* c, int32_t n_groups, const gbr_drive_group* groups, int32_t d_in, int32_t hidden,
+              void* stream) {
+  if (!c || n_groups < 1 || !groups || d_in < 1 || d_in > 1024 || hidden < 1 || hidden > 1024)
+    return GBR_ERR_INVALID_ARG;
+  for (int i = 0; i < n_groups; ++i) {
+    const gbr_drive_group& g = groups[i];
+    if (!g.mlp || !g.theta || !g.bases || !g.psi || !g.raw || g.B < 1 || g.K < 1 || g.K > kMaxK || g.N < 1)
+      return GBR_ERR_INVALID_ARG;
+    if (g.B > kBlendMaxFrames || blend_drive_blocks(g.N) > INT32_MAX) return GBR_ERR_INVALID_ARG;
+    if (g.B > c->cap_frames) return GBR_ERR_CAPACITY;
+  }
+  for (int i0 = 0; i0 < n_groups;) {
+    // as many groups as a launch's table, the weight table and a grid hold
+    DriveTable t;
+    int64_t frames = 0, blocks = 0;
+    int n = 0, max_K = 0;
+    for (; n < kDriveGroups && i0 + n < n_groups; ++n) {
+      const gbr_drive_group& g = groups[i0 + n];
+      const int64_t nb = blend_drive_blocks(g.N);
+      if (n > 0 && (frames + g.B > kBlendMaxFrames || blocks + nb > INT32_MAX)) break;
+      t.g[n] = DriveGroup{g.mlp, g.theta, g.bases, g.psi, g.raw, g.N, g.B, g.K};
+      t.frame0[n] = (uint32_t)frames;
+      t.block0[n] = (uint32_t)blocks;
+      frames += g.B;
+      blocks += nb;
+      max_K = std::max(max_K, (int)g.K);
+    }
+    for (int k = n; k < kDriveGroups; ++k) {
+      t.g[k] = DriveGroup{};
+      t.frame0[k] = t.block0[k] = 0xffffffffu;
+    }
+    t.frames = (uint32_t)frames;
+    t.blocks = (uint32_t)blocks;
+    t.w64 = c->blend_w64;
+    {
+      KTimer k(c, GBR_K_MLP, (hipStream_t)stream);
+      launch_mlp_drive(t, d_in, hidden, (hipStream_t)stream);
+    }
+    {
+      KTimer k(c, GBR_K_BLEND, (hipStream_t)stream);
+      launch_blend_drive(t, max_K, (hipStream_t)stream);
+    }
+    GBR_HIP(hipGetLastError());
+    i0 += n;
+  }
+  return GBR_OK;
+}
+
 int gbr_mlp_backward(gbr_ctx* c, const float* params, const float* dpsi, float* dparams, void* stream) {
   if (!c || !params || !dpsi || !dparams) return GBR_ERR_INVALID_ARG;
   if (!c->have_mlp) return GBR_ERR_STATE;

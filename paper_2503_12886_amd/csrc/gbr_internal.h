@@ -242,6 +242,30 @@ void launch_fill_f32(float* p, float v, int64_t n, hipStream_t s);
 constexpr int kBucketBlock = 8192;      // splats per workgroup in the depth-bucket passes
 constexpr int kBlendMaxFrames = 4096;   // frames per gbr_blend call (rows of the float64 weight table)
 constexpr int kBlendW64Stride = 64;     // K + 1 <= 64
+
+// Models driven together (gbr_drive), in a kernel's arguments.
+constexpr int kDriveGroups = 16;
+struct DriveGroup {
+  const float *mlp, *theta, *bases;
+  float *psi, *raw;
+  int64_t N;
+  int32_t B, K;
+};
+struct DriveTable {
+  DriveGroup g[kDriveGroups];
+  uint32_t frame0[kDriveGroups], block0[kDriveGroups];   // first frame and blend workgroup; 0xffffffff past the last
+  uint32_t frames, blocks;
+  double* w64;                                           // [frames][kBlendW64Stride]
+  __device__ __forceinline__ int group_of(const uint32_t (&first)[kDriveGroups], uint32_t x) const {
+    int i = 0;
+#pragma unroll
+    for (int k = 1; k < kDriveGroups; ++k) i += x >= first[k] ? 1 : 0;
+    return i;
+  }
+};
+int64_t blend_drive_blocks(int64_t N);
+void launch_mlp_drive(const DriveTable& t, int d_in, int hidden, hipStream_t s);
+void launch_blend_drive(const DriveTable& t, int max_K, hipStream_t s);
 void launch_blend_fwd(const float* bases, const float* weights, int B, int K, int64_t N, float* raw, double* w64,
                       hipStream_t s);
 void launch_blend_bwd(const float* draw, const float* bases, const float* weights, int B, int K, int64_t N,

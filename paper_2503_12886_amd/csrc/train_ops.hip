@@ -105,25 +105,32 @@ __device__ __forceinline__ void mlp_products(const float (&wv)[R][T4], const flo
   }
 }
 
+// Where a layer's units go: memory, LDS, float64 in memory (null: not there).
+struct MlpOut {
+  float* g;
+  float* l;
+  double* d;
+};
+
 // out[j0 + i] = bias + the sums, i < R
 template <int R>
 __device__ __forceinline__ void mlp_store(float (&s)[R], const float* __restrict__ bias, int n_out, int j0,
-                                          float* __restrict__ out_g, float* out_l) {
+                                          MlpOut out) {
   const int lane = threadIdx.x & 63;
   const float tot = wave_sums(s);
   const int j = j0 + lane * R / 64;
   if (lane % (64 / R) == 0 && j < n_out) {
     const float v = tot + bias[j];
-    out_g[j] = v;
-    if (out_l) out_l[j] = v;
+    if (out.g) out.g[j] = v;
+    if (out.l) out.l[j] = v;
+    if (out.d) out.d[j] = (double)v;
   }
 }
 
 // out[j] = bias[j] + sum_c W[j][c] act(in[c]) for j < n_out; act = ReLU when relu_in.
 template <int R>
 __device__ __forceinline__ void mlp_layer(const float* __restrict__ W, const float* __restrict__ bias,
-                                          const float* in, int n_in, int n_out, bool relu_in,
-                                          float* __restrict__ out_g, float* out_l) {
+                                          const float* in, int n_in, int n_out, bool relu_in, MlpOut out) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int j0 = w * R; j0 < n_out; j0 += kMlpWaves * R) {
     float s[R];
@@ -134,32 +141,29 @@ __device__ __forceinline__ void mlp_layer(const float* __restrict__ W, const flo
       mlp_weights(W, n_in, n_out, j0, c0, wv);
       mlp_products(wv, in, n_in, c0, relu_in, s);
     }
-    mlp_store(s, bias, n_out, j0, out_g, out_l);
+    mlp_store(s, bias, n_out, j0, out);
   }
 }
 
-// HELD: inputs up to 64 and hidden layers up to 256 (a block of rows per
-// wave): the three layers' weights are read at once.
+// One frame's three layers.  z1, z2 (may be null): its pre-activations; psi64
+// (may be null): its outputs as float64.  HELD: inputs up to 64 and hidden
+// layers up to 256 (a block of rows per wave): the three layers' weights are
+// read at once.
 template <bool HELD>
-__global__ __launch_bounds__(kMlpThreads) void mlp_fwd_kernel(const float* __restrict__ params,
-                                                              const float* __restrict__ theta, int d_in, int hidden,
-                                                              int K, float* __restrict__ psi, float* __restrict__ z1,
-                                                              float* __restrict__ z2) {
+__device__ __forceinline__ void mlp_frame(const float* __restrict__ params, const float* __restrict__ theta, int d_in,
+                                          int hidden, int K, float* __restrict__ psi, float* __restrict__ z1,
+                                          float* __restrict__ z2, double* __restrict__ psi64) {
   __shared__ float xa[kMlpMaxIn], xb[kMlpMaxIn];
-  const int b = blockIdx.x;
   const float* W1 = params;
   const float* b1 = W1 + (int64_t)hidden * d_in;
   const float* W2 = b1 + hidden;
   const float* b2 = W2 + (int64_t)hidden * hidden;
   const float* W3 = b2 + hidden;
   const float* b3 = W3 + (int64_t)K * hidden;
-  z1 += (int64_t)b * hidden;
-  z2 += (int64_t)b * hidden;
-  psi += (int64_t)b * K;
   if constexpr (HELD) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j0 = w * kMlpRows, k0 = w * kMlpRowsOut;
-    const float th = (int)threadIdx.x < d_in ? theta[(int64_t)b * d_in + threadIdx.x] : 0.0f;
+    const float th = (int)threadIdx.x < d_in ? theta[threadIdx.x] : 0.0f;
     float w1[kMlpRows][1], w2[kMlpRows][4], w3[kMlpRowsOut][4];
     mlp_weights(W1, d_in, hidden, j0, 0, w1);
     mlp_weights(W2, hidden, hidden, j0, 0, w2);
@@ -171,34 +175,70 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_fwd_kernel(const float* __res
 #pragma unroll
     for (int r = 0; r < kMlpRows; ++r) s[r] = 0.0f;
     mlp_products(w1, xa, d_in, 0, false, s);
-    mlp_store(s, b1, hidden, j0, z1, xb);
+    mlp_store(s, b1, hidden, j0, MlpOut{z1, xb, nullptr});
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kMlpRows; ++r) s[r] = 0.0f;
     mlp_products(w2, xb, hidden, 0, true, s);
-    mlp_store(s, b2, hidden, j0, z2, xa);
+    mlp_store(s, b2, hidden, j0, MlpOut{z2, xa, nullptr});
     __syncthreads();
     if (k0 < K) {
 #pragma unroll
       for (int r = 0; r < kMlpRowsOut; ++r) so[r] = 0.0f;
       mlp_products(w3, xa, hidden, 0, true, so);
-      mlp_store(so, b3, K, k0, psi, nullptr);
+      mlp_store(so, b3, K, k0, MlpOut{psi, nullptr, psi64});
     }
   } else {
-    for (int t = threadIdx.x; t < d_in; t += kMlpThreads) xa[t] = theta[(int64_t)b * d_in + t];
+    for (int t = threadIdx.x; t < d_in; t += kMlpThreads) xa[t] = theta[t];
     __syncthreads();
-    mlp_layer<kMlpRows>(W1, b1, xa, d_in, hidden, false, z1, xb);
+    mlp_layer<kMlpRows>(W1, b1, xa, d_in, hidden, false, MlpOut{z1, xb, nullptr});
     __syncthreads();
-    mlp_layer<kMlpRows>(W2, b2, xb, hidden, hidden, true, z2, xa);
+    mlp_layer<kMlpRows>(W2, b2, xb, hidden, hidden, true, MlpOut{z2, xa, nullptr});
     __syncthreads();
-    mlp_layer<kMlpRowsOut>(W3, b3, xa, hidden, K, true, psi, nullptr);
+    mlp_layer<kMlpRowsOut>(W3, b3, xa, hidden, K, true, MlpOut{psi, nullptr, psi64});
   }
+}
+
+template <bool HELD>
+__global__ __launch_bounds__(kMlpThreads) void mlp_fwd_kernel(const float* __restrict__ params,
+                                                              const float* __restrict__ theta, int d_in, int hidden,
+                                                              int K, float* __restrict__ psi, float* __restrict__ z1,
+                                                              float* __restrict__ z2) {
+  const int64_t b = blockIdx.x;
+  mlp_frame<HELD>(params, theta + b * d_in, d_in, hidden, K, psi + b * K, z1 + b * hidden, z2 + b * hidden, nullptr);
+}
+
+// The MLPs of several models (gbr_drive): a workgroup per frame of all of them,
+// which also leaves the frame's row of the blend's weight table.  A model at a
+// time has one CU or a few at work and each launch's gap: 8 models of one
+// frame, 56-256-256-20, 8 x 9.4 us -> 12.2.
+template <bool HELD>
+__global__ __launch_bounds__(kMlpThreads) void mlp_drive_kernel(DriveTable t, int d_in, int hidden) {
+  const int gi = t.group_of(t.frame0, blockIdx.x);
+  const DriveGroup& g = t.g[gi];
+  const int64_t b = blockIdx.x - t.frame0[gi];
+  double* w64 = t.w64 + (int64_t)blockIdx.x * kBlendW64Stride;
+  const int k = threadIdx.x;
+  if (k == 0 || (k > g.K && k < kBlendW64Stride)) w64[k] = k == 0 ? 1.0 : 0.0;   // the implicit 1 of slice 0
+  mlp_frame<HELD>(g.mlp, g.theta + b * d_in, d_in, hidden, g.K, g.psi + b * g.K, nullptr, nullptr, w64 + 1);
+}
+
+static bool mlp_held(int d_in, int hidden, int K) {
+  return d_in <= 64 && hidden <= kMlpWaves * kMlpRows && K <= kMlpWaves * kMlpRowsOut;
+}
+
+void launch_mlp_drive(const DriveTable& t, int d_in, int hidden, hipStream_t s) {
+  // (K <= 63 always fits)
+  if (mlp_held(d_in, hidden, kBlendW64Stride - 1))
+    hipLaunchKernelGGL(mlp_drive_kernel<true>, dim3(t.frames), dim3(kMlpThreads), 0, s, t, d_in, hidden);
+  else
+    hipLaunchKernelGGL(mlp_drive_kernel<false>, dim3(t.frames), dim3(kMlpThreads), 0, s, t, d_in, hidden);
 }
 
 void launch_mlp_fwd(const float* params, const float* theta, int B, int d_in, int hidden, int K, float* psi,
                     float* z1, float* z2, hipStream_t s) {
   if (B == 0) return;
-  if (d_in <= 64 && hidden <= kMlpWaves * kMlpRows && K <= kMlpWaves * kMlpRowsOut)
+  if (mlp_held(d_in, hidden, K))
     hipLaunchKernelGGL(mlp_fwd_kernel<true>, dim3(B), dim3(kMlpThreads), 0, s, params, theta, d_in, hidden, K, psi, z1,
                        z2);
   else

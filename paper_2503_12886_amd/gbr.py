@@ -45,6 +45,12 @@ class gbr_config(ctypes.Structure):
                 ("max_entries", ctypes.c_int64)]
 
 
+class gbr_drive_group(ctypes.Structure):
+    _fields_ = [("mlp", ctypes.c_void_p), ("theta", ctypes.c_void_p), ("bases", ctypes.c_void_p),
+                ("psi", ctypes.c_void_p), ("raw", ctypes.c_void_p), ("N", ctypes.c_int64), ("B", ctypes.c_int32),
+                ("K", ctypes.c_int32)]
+
+
 class gbr_status(ctypes.Structure):
     _fields_ = [("entries", ctypes.c_int64), ("entries_capacity", ctypes.c_int64), ("overflow", ctypes.c_int32),
                 ("adam_steps", ctypes.c_int32 * 4), ("loss", ctypes.c_float)]
@@ -80,6 +86,7 @@ _SIGS = {
                             _vp, _vp], ctypes.c_int),
     "gbr_loss": ([_vp, _vp, _vp, _i32, _vp, _vp], ctypes.c_int),
     "gbr_mlp_forward": ([_vp, _vp, _vp, _i32, _i32, _i32, _i32, _vp, _vp], ctypes.c_int),
+    "gbr_drive": ([_vp, _i32, ctypes.POINTER(gbr_drive_group), _i32, _i32, _vp], ctypes.c_int),
     "gbr_mlp_backward": ([_vp, _vp, _vp, _vp, _vp], ctypes.c_int),
     "gbr_adam_step": ([_vp, _i32, _vp, _vp, _vp, _vp, _i64, _i64, ctypes.POINTER(_f32), _f32, _f32, _f32, _vp],
                       ctypes.c_int),
@@ -426,11 +433,39 @@ def gbr_loss(ctx: Context, images, targets, kind: int, dimages, stream=None) -> 
                           _f32dev(dimages, "dimages"), _stream(stream)), "gbr_loss")
 
 
+def mlp_params(d_in: int, hidden: int, K: int) -> int:
+    """Floats of a packed MLP."""
+    return hidden * d_in + hidden + hidden * hidden + hidden + K * hidden + K
+
+
 def gbr_mlp_forward(ctx: Context, params, theta, d_in: int, hidden: int, K: int, psi, stream=None) -> None:
     B = theta.shape[0]
-    n = hidden * d_in + hidden + hidden * hidden + hidden + K * hidden + K
+    n = mlp_params(d_in, hidden, K)
     _check(lib().gbr_mlp_forward(ctx.handle, _f32dev(params, "params", n), _f32dev(theta, "theta", B * d_in), B,
                                  d_in, hidden, K, _f32dev(psi, "psi", B * K), _stream(stream)), "gbr_mlp_forward")
+
+
+def gbr_drive(ctx: Context, groups, d_in: int, hidden: int, stream=None) -> None:
+    """gbr_mlp_forward and gbr_blend of several models in two launches: groups
+    are (mlp, theta [B][d_in], bases [K+1][N][16], psi [B][K], raw [B][N][16]),
+    or an array of gbr_drive_group that the caller has filled and checked."""
+    if isinstance(groups, ctypes.Array):
+        _check(lib().gbr_drive(ctx.handle, len(groups), groups, d_in, hidden, _stream(stream)), "gbr_drive")
+        return
+    arr = (gbr_drive_group * len(groups))()
+    for g, (mlp, theta, bases, psi, raw) in zip(arr, groups):
+        B = theta.shape[0]
+        K1, N, F = bases.shape
+        K = K1 - 1
+        if F != 16 or raw.shape != (B, N, 16) or psi.shape != (B, K):
+            raise ValueError("gbr_drive: shape mismatch")
+        g.mlp = _f32dev(mlp, "params", mlp_params(d_in, hidden, K))
+        g.theta = _f32dev(theta, "theta", B * d_in)
+        g.bases = _f32dev(bases, "bases")
+        g.psi = _f32dev(psi, "psi")
+        g.raw = _f32dev(raw, "raw")
+        g.N, g.B, g.K = N, B, K
+    gbr_drive(ctx, arr, d_in, hidden, stream)
 
 
 def gbr_mlp_backward(ctx: Context, params, dpsi, dparams, stream=None) -> None:

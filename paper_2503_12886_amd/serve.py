@@ -291,6 +291,7 @@ class GpuExecutor:
                 "images": torch.zeros(max_batch * 3 * width * height, device=dev),
                 "event": torch.cuda.Event(),
             })
+            self.slots[-1]["theta_np"] = self.slots[-1]["theta_h"].numpy()
 
     def enqueue(self, slot: int, batch: List[Request]):
         """Every kernel of one batch on the slot's stream; returns the image offsets."""
@@ -299,9 +300,19 @@ class GpuExecutor:
         frames = [batch[i] for i in order]
         with self.torch.cuda.stream(S["stream"]):
             for i, r in enumerate(frames):
-                S["theta_h"][i].copy_(self.torch.from_numpy(np.asarray(r.theta, np.float32)))
+                theta = np.asarray(r.theta, np.float32)
+                if theta.shape == (self.d_in,):
+                    S["theta_np"][i] = theta
+                else:
+                    S["theta_h"][i].copy_(self.torch.from_numpy(theta))
             S["theta"][:len(frames)].copy_(S["theta_h"][:len(frames)], non_blocking=True)
+            # the frames of an avatar are a group: their rows of theta, psi and
+            # raw follow one another (as addresses: the GPU waits for this loop, and
+            # slices of the tensors and a tensor copy per theta cost 11 us a group)
             offsets = [0]
+            groups = []
+            kmax = S["psi"].shape[1]
+            theta_p, psi_p, raw_p = S["theta"].data_ptr(), S["psi"].data_ptr(), S["raw"].data_ptr()
             i = 0
             while i < len(frames):
                 a = frames[i].avatar
@@ -309,14 +320,17 @@ class GpuExecutor:
                 while j < len(frames) and frames[j].avatar == a:
                     j += 1
                 n, N, K = j - i, self.N[a], self.K[a]
-                kmax = S["psi"].shape[1]
-                psi = S["psi"].view(-1)[i * kmax:i * kmax + n * K].view(n, K)   # disjoint per group
-                gbr.gbr_mlp_forward(S["ctx"], self.mlp[a], S["theta"][i:j], self.d_in, self.hidden, K, psi)
-                raw = S["raw"].view(-1)[offsets[-1] * 16:(offsets[-1] + n * N) * 16].view(n, N, 16)
-                gbr.gbr_blend(S["ctx"], self.bases[a], psi, raw)
+                if j > S["psi"].shape[0] or offsets[-1] + n * N > S["raw"].shape[0]:
+                    raise ValueError("the batch exceeds the slot")
+                mlp = gbr._f32dev(self.mlp[a], "params", gbr.mlp_params(self.d_in, self.hidden, K))
+                groups.append(gbr.gbr_drive_group(mlp, theta_p + i * self.d_in * 4,
+                                                  gbr._f32dev(self.bases[a], "bases", (K + 1) * N * 16),
+                                                  psi_p + i * kmax * 4, raw_p + offsets[-1] * 64, N, n, K))
                 for _ in range(n):
                     offsets.append(offsets[-1] + N)
                 i = j
+            if groups:
+                gbr.gbr_drive(S["ctx"], (gbr.gbr_drive_group * len(groups))(*groups), self.d_in, self.hidden)
             gbr.gbr_render(S["ctx"], S["raw"], offsets, [r.cam for r in frames], S["images"])
             S["event"].record(S["stream"])
         out = {}
