@@ -405,8 +405,8 @@ int enqueue_preprocess(gbr_ctx* c, const float* raw, hipStream_t s) {
   {
     KTimer t(c, GBR_K_DEPTH_ORDER, s);
     // the scan of the splats' tile counts (preprocess output) shares the bucket scan's launches
-    const ScanJob splat_scan{c->cnt, c->soff, c->n_splats, c->scan_scratch_splat, -1, nullptr, nullptr, 1};
-    launch_depth_order(a, c->max_frame_splats, c->scan_scratch, splat_scan, s);
+    const ScanJob splat_scan{c->cnt, c->soff, c->n_splats, c->scan_scratch_splat, -1, nullptr};
+    launch_depth_order(a, c->max_frame_splats, splat_scan, s);
   }
   {
     KTimer t(c, GBR_K_BINNING, s);

@@ -104,8 +104,8 @@ struct PassArgs {
   uint32_t* blk_mm;         // [2 per projection workgroup] min, max binary32 depth bits of its valid splats;
                             // frame b's workgroup j at gauss_base / 256 + b + j (frames never share one);
                             // the backward pass leaves the workgroup's number of hits in the first word
-  uint32_t* bkt_count;      // [B * nbk][nblk] per-block bucket counts
-  uint32_t* bkt_moff;       // [B * nbk * nblk + 1] their exclusive scan
+  uint32_t* bkt_count;      // [B][nblk][nbk] per-block bucket counts
+  uint32_t* bkt_moff;       // [B][nblk][nbk] each block's first place in each bucket
   uint32_t* bkt_start;      // [B * nbk + 1] exclusive scan; frame b's valid splats start at bkt_start[b * nbk]
   unsigned long long* bkeys;      // [S] (depth bits << 32) | splat, grouped by bucket
   unsigned long long* bkeys_alt;  // [S] ping-pong for large buckets
@@ -274,11 +274,9 @@ void launch_blend_bwd(const float* draw, const float* bases, const float* weight
 int64_t blend_bwd_partials(int B, int K, int64_t N);
 // an upper bound of the floats of partials launch_blend_bwd writes and reads for this shape
 int64_t blend_bwd_partials_used(int B, int K, int64_t N);
-// Exclusive scan of in[0, n) into out[0, n] (out[n] = total).  With strided
-// non-null, also strided[j] = out[j * stride] for every j * stride <= n.
-// The grand total is stored to total_out when non-null, and sets the
-// overflow flag when it exceeds cap_check (>= 0).  block_sums holds
-// scan_scratch_words(n) words.
+// Exclusive scan of in[0, n) into out[0, n] (out[n] = total).  The grand total
+// is stored to total_out when non-null, and sets the overflow flag when it
+// exceeds cap_check (>= 0).  block_sums holds scan_scratch_words(n) words.
 struct ScanJob {
   const uint32_t* in;
   uint32_t* out;
@@ -286,14 +284,10 @@ struct ScanJob {
   uint32_t* block_sums;
   int64_t cap_check;
   unsigned long long* total_out;
-  uint32_t* strided;
-  int stride;
 };
-void launch_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* block_sums, StatusDev* status,
-                     int64_t cap_check, unsigned long long* total_out, hipStream_t s, uint32_t* strided = nullptr,
-                     int stride = 1);
-// Two independent scans in the same two launches (distinct block_sums).
-void launch_scan_u32_pair(const ScanJob& j0, const ScanJob& j1, StatusDev* status, hipStream_t s);
+void launch_scan(const ScanJob& J, StatusDev* status, hipStream_t s);
+// The depth buckets' scan (bkt_count -> bkt_start, bkt_moff) and, in the same launches, another.
+void launch_bucket_scan(const PassArgs& a, const ScanJob& side, hipStream_t s);
 int64_t scan_scratch_words(int64_t n);
 // Returns whether it launched (no frame has Gaussians otherwise): the
 // launch also clears the pass's counters.
@@ -314,8 +308,7 @@ void launch_tile_scan_classify(const PassArgs& a, uint32_t* block_sums, int64_t 
 
 // The depth order of every frame's splats.  side is an independent scan whose
 // input is ready when the pass starts, run in the bucket scan's launches.
-void launch_depth_order(const PassArgs& a, int64_t max_frame_splats, uint32_t* scan_scratch, const ScanJob& side,
-                        hipStream_t s);
+void launch_depth_order(const PassArgs& a, int64_t max_frame_splats, const ScanJob& side, hipStream_t s);
 void launch_composite_fwd(const PassArgs& a, float* images, hipStream_t s);
 void launch_composite_bwd(const PassArgs& a, const float* dimages, const float* images, int chunk, hipStream_t s);
 void launch_gather_bwd(const PassArgs& a, const float* raw, float* draw, int64_t max_frame_splats, hipStream_t s);

@@ -29,33 +29,12 @@ void launch_fill_f32(float* p, float v, int64_t n, hipStream_t s) {
 // per-block totals, then every block adds the totals of the blocks before it
 // (read directly, summed in 64 bits) to its own rescan.  The grand total is
 // published (and checked against a capacity) by the workgroup that writes
-// out[n].  Integer sums, so the order does not matter for the result.  One
-// launch pair can carry two independent scans: the first job's blocks come
-// first in the grid, then the second's.
+// out[n].  Integer sums, so the order does not matter for the result.  The
+// depth buckets' scan (below) and one of this kind share a launch pair: the
+// buckets' blocks come first in the grid.
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanBlock = kScanThreads * kScanItems;
-
-struct ScanJobs {
-  ScanJob j0, j1;
-  int nb0;   // blocks of the first job
-};
-
-// The job of this workgroup (chosen field by field, uniformly) and its block index within it.
-__device__ __forceinline__ ScanJob scan_job(const ScanJobs& J, int* blk) {
-  const bool second = (int)blockIdx.x >= J.nb0;
-  *blk = (int)blockIdx.x - (second ? J.nb0 : 0);
-  ScanJob j;
-  j.in = second ? J.j1.in : J.j0.in;
-  j.out = second ? J.j1.out : J.j0.out;
-  j.n = second ? J.j1.n : J.j0.n;
-  j.block_sums = second ? J.j1.block_sums : J.j0.block_sums;
-  j.cap_check = second ? J.j1.cap_check : J.j0.cap_check;
-  j.total_out = second ? J.j1.total_out : J.j0.total_out;
-  j.strided = second ? J.j1.strided : J.j0.strided;
-  j.stride = second ? J.j1.stride : J.j0.stride;
-  return j;
-}
 
 __device__ __forceinline__ void publish_total(unsigned long long total, StatusDev* status, int64_t cap_check,
                                               unsigned long long* total_out) {
@@ -82,25 +61,78 @@ __device__ __forceinline__ void scan_totals_block(const ScanJob& J, int blk, uin
   if (threadIdx.x == 0) J.block_sums[blk] = tot;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_totals_kernel(ScanJobs jobs) {
-  __shared__ uint32_t lw[kScanThreads / 64];
-  int blk;
-  const ScanJob J = scan_job(jobs, &blk);
-  scan_totals_block(J, blk, lw);
+// The scan of the depth buckets: bkt_count holds a row of nbk counts per (frame,
+// block of splats); a bucket's start is the number of splats in the buckets
+// before it, and each block's offset in a bucket follows the blocks before
+// it.  A workgroup takes kBktScan buckets, two to a thread, and reads every
+// block's row of them (rows are contiguous, for the count and the scatter pass
+// as well: with a bucket's blocks adjacent, each of those passes' accesses was
+// a line of its own).  The totals lie in the tiles' bitmap rows, which are
+// built later: at least 32 words a frame, where 16 are used.
+constexpr int kBktScan = 2 * kScanThreads;
+
+struct BucketPair {
+  const uint32_t* row;       // the pair's counts in the first block's row
+  int64_t out;               // and its index in the buckets; < 0: none
+};
+__device__ __forceinline__ BucketPair bucket_pair(const PassArgs& a, int blk) {
+  const int64_t k = (int64_t)blk * kBktScan + 2 * threadIdx.x;   // (nbk is a power of two >= 64: a pair has one frame)
+  if (k >= (int64_t)a.B * a.nbk) return BucketPair{a.bkt_count, -1};
+  const int64_t b = k / a.nbk;
+  return BucketPair{a.bkt_count + b * a.nblk * a.nbk + k % a.nbk, k};
+}
+__device__ __forceinline__ uint2 bucket_sums(const PassArgs& a, const BucketPair& P) {
+  uint2 c = make_uint2(0u, 0u);
+#pragma unroll 8
+  for (int j = 0; j < a.nblk; ++j) {
+    const uint2 v = *reinterpret_cast<const uint2*>(P.row + (int64_t)j * a.nbk);
+    c.x += v.x;
+    c.y += v.y;
+  }
+  return P.out < 0 ? make_uint2(0u, 0u) : c;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(ScanJobs jobs, StatusDev* status) {
+__global__ __launch_bounds__(kScanThreads) void order_totals_kernel(PassArgs a, ScanJob side, int nb0) {
+  __shared__ uint32_t lw[kScanThreads / 64];
+  if ((int)blockIdx.x >= nb0) return scan_totals_block(side, (int)blockIdx.x - nb0, lw);
+  const uint2 c = bucket_sums(a, bucket_pair(a, (int)blockIdx.x));
+  uint32_t tot;
+  block_excl_scan<kScanThreads>(c.x + c.y, lw, &tot);
+  if (threadIdx.x == 0) a.tbits[blockIdx.x] = tot;
+}
+
+__device__ __forceinline__ void bucket_apply_block(const PassArgs& a, int blk) {
+  __shared__ uint32_t lw[kScanThreads / 64];
+  __shared__ uint32_t wsum[kScanThreads / 64];
+  const BucketPair P = bucket_pair(a, blk);
+  const uint2 c = bucket_sums(a, P);
+  uint32_t part = 0;
+  for (int k = threadIdx.x; k < blk; k += kScanThreads) part += a.tbits[k];
+  part = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(part), 63);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = part;
+  const uint32_t ex = block_excl_scan<kScanThreads>(c.x + c.y, lw, nullptr);   // (orders wsum as well)
+  if (P.out < 0) return;
+  uint32_t x = ex + ((wsum[0] + wsum[1]) + (wsum[2] + wsum[3])), y = x + c.x;
+  *reinterpret_cast<uint2*>(a.bkt_start + P.out) = make_uint2(x, y);
+  if (P.out + 2 == (int64_t)a.B * a.nbk) a.bkt_start[P.out + 2] = y + c.y;
+  uint32_t* out = a.bkt_moff + (P.row - a.bkt_count);
+#pragma unroll 8
+  for (int j = 0; j < a.nblk; ++j) {
+    const uint2 v = *reinterpret_cast<const uint2*>(P.row + (int64_t)j * a.nbk);
+    *reinterpret_cast<uint2*>(out + (int64_t)j * a.nbk) = make_uint2(x, y);
+    x += v.x;
+    y += v.y;
+  }
+}
+
+__device__ __forceinline__ void scan_apply_block(const ScanJob& J, int blk, StatusDev* status) {
   __shared__ uint32_t tile[kScanBlock];
   __shared__ uint32_t lw[kScanThreads / 64];
   __shared__ unsigned long long wsum[kScanThreads / 64];
-  int blk;
-  const ScanJob J = scan_job(jobs, &blk);
   const uint32_t* __restrict__ in = J.in;
   const uint32_t* __restrict__ block_sums = J.block_sums;
   uint32_t* __restrict__ out = J.out;
-  uint32_t* __restrict__ strided = J.strided;
   const int64_t n = J.n;
-  const int stride = J.stride;
   const int64_t base = (int64_t)blk * kScanBlock;
   uint32_t v[kScanItems];
 #pragma unroll
@@ -138,38 +170,42 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(ScanJobs jobs,
     if (k < n) {
       const uint32_t val = (uint32_t)(off + tile[idx]);
       out[k] = val;
-      if (strided && (uint32_t)k % (uint32_t)stride == 0u) strided[(uint32_t)k / (uint32_t)stride] = val;
     }
   }
   // out[n] = grand total, written by the block that holds position n
   if (threadIdx.x == kScanThreads - 1 && base <= n && n < base + kScanBlock) {
     const unsigned long long total = off + ex;   // ex of the last thread: the block's running total
     out[n] = (uint32_t)total;
-    if (strided && (uint32_t)n % (uint32_t)stride == 0u) strided[(uint32_t)n / (uint32_t)stride] = (uint32_t)total;
     publish_total(total, status, J.cap_check, J.total_out);
   }
 }
 
+__global__ __launch_bounds__(kScanThreads) void order_apply_kernel(PassArgs a, ScanJob side, int nb0) {
+  if ((int)blockIdx.x >= nb0) scan_apply_block(side, (int)blockIdx.x - nb0, a.status);
+  else bucket_apply_block(a, (int)blockIdx.x);
+}
+
+__global__ __launch_bounds__(kScanThreads) void scan_totals_kernel(ScanJob J) {
+  __shared__ uint32_t lw[kScanThreads / 64];
+  scan_totals_block(J, (int)blockIdx.x, lw);
+}
+__global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(ScanJob J, StatusDev* status) {
+  scan_apply_block(J, (int)blockIdx.x, status);
+}
+
 int64_t scan_scratch_words(int64_t n) { return div_up(n + 1, kScanBlock) + 1; }
 
-void launch_scan_u32_pair(const ScanJob& j0, const ScanJob& j1, StatusDev* status, hipStream_t s) {
-  ScanJobs J;
-  J.j0 = j0;
-  J.j1 = j1;
-  J.j0.stride = j0.stride < 1 ? 1 : j0.stride;
-  J.j1.stride = j1.stride < 1 ? 1 : j1.stride;
-  J.nb0 = (int)div_up(j0.n + 1, kScanBlock);
-  const int nb = J.nb0 + (j1.in ? (int)div_up(j1.n + 1, kScanBlock) : 0);
+void launch_scan(const ScanJob& J, StatusDev* status, hipStream_t s) {
+  const int nb = (int)div_up(J.n + 1, kScanBlock);
   hipLaunchKernelGGL(scan_totals_kernel, dim3(nb), dim3(kScanThreads), 0, s, J);
   hipLaunchKernelGGL(scan_apply_kernel, dim3(nb), dim3(kScanThreads), 0, s, J, status);
 }
 
-void launch_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* block_sums, StatusDev* status,
-                     int64_t cap_check, unsigned long long* total_out, hipStream_t s, uint32_t* strided,
-                     int stride) {
-  const ScanJob j0{in, out, n, block_sums, cap_check, total_out, strided, stride};
-  const ScanJob none{nullptr, nullptr, 0, nullptr, -1, nullptr, nullptr, 1};
-  launch_scan_u32_pair(j0, none, status, s);
+void launch_bucket_scan(const PassArgs& a, const ScanJob& side, hipStream_t s) {
+  const int nb0 = (int)div_up((int64_t)a.B * a.nbk, kBktScan);
+  const dim3 grid(nb0 + (int)div_up(side.n + 1, kScanBlock));
+  hipLaunchKernelGGL(order_totals_kernel, grid, dim3(kScanThreads), 0, s, a, side, nb0);
+  hipLaunchKernelGGL(order_apply_kernel, grid, dim3(kScanThreads), 0, s, a, side, nb0);
 }
 
 // ---------------------------------------------------------------- preprocess
@@ -527,22 +563,20 @@ void launch_classify_tiles(const PassArgs& a, bool backward, hipStream_t s) {
 
 // The tile scan's totals pass (workgroups [0, nb)) and the forward
 // classification (the rest, 1024 tiles each) in one launch.
-__global__ __launch_bounds__(kScanThreads) void tile_totals_classify_kernel(ScanJobs jobs, PassArgs a) {
+__global__ __launch_bounds__(kScanThreads) void tile_totals_classify_kernel(ScanJob J, int nb0, PassArgs a) {
   __shared__ uint32_t lw[kScanThreads / 64];
   __shared__ uint32_t cnt[33], base[33];
-  if ((int)blockIdx.x < jobs.nb0) scan_totals_block(jobs.j0, (int)blockIdx.x, lw);
-  else classify_block<kScanThreads>(a, (int)blockIdx.x - jobs.nb0, false, cnt, base);
+  if ((int)blockIdx.x < nb0) scan_totals_block(J, (int)blockIdx.x, lw);
+  else classify_block<kScanThreads>(a, (int)blockIdx.x - nb0, false, cnt, base);
 }
 
 void launch_tile_scan_classify(const PassArgs& a, uint32_t* block_sums, int64_t cap_check,
                                unsigned long long* total_out, hipStream_t s) {
-  ScanJobs J;
-  J.j0 = ScanJob{a.tile_count, a.tile_start, a.n_tiles, block_sums, cap_check, total_out, nullptr, 1};
-  J.j1 = ScanJob{nullptr, nullptr, 0, nullptr, -1, nullptr, nullptr, 1};
-  J.nb0 = (int)div_up((int64_t)a.n_tiles + 1, kScanBlock);
+  const ScanJob J{a.tile_count, a.tile_start, a.n_tiles, block_sums, cap_check, total_out};
+  const int nb0 = (int)div_up((int64_t)a.n_tiles + 1, kScanBlock);
   const int ncls = a.n_tiles > 0 ? div_up(a.n_tiles, 1024) : 0;
-  hipLaunchKernelGGL(tile_totals_classify_kernel, dim3(J.nb0 + ncls), dim3(kScanThreads), 0, s, J, a);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3(J.nb0), dim3(kScanThreads), 0, s, J, a.status);
+  hipLaunchKernelGGL(tile_totals_classify_kernel, dim3(nb0 + ncls), dim3(kScanThreads), 0, s, J, nb0, a);
+  hipLaunchKernelGGL(scan_apply_kernel, dim3(nb0), dim3(kScanThreads), 0, s, J, a.status);
 }
 
 // ---------------------------------------------------------------- complete lists
