@@ -34,8 +34,9 @@ __device__ __forceinline__ uint32_t depth_bucket(uint32_t bits, uint32_t mn, flo
 // block its own range inside every bucket.  (With a bucket's blocks adjacent
 // in the matrix, every count was stored and read on a line of its own: count
 // and scatter pass 9.8 + 14.0 -> 5.4 + 13.0 us for 16 frames of 50k splats, 43
-// + 89 -> 20 + 80 for 64 of 100k; the two scan launches 10.4 -> 11.3, 24 -> 35.)  The scatter pass recomputes the
-// buckets and places each splat at its block's offset plus its LDS rank.
+// + 89 -> 20 + 80 for 64 of 100k; the two scan launches 10.4 -> 11.3, 24 -> 35.)
+// The scatter pass recomputes the buckets and places each splat at its block's
+// offset plus its LDS rank.
 // Depth keys come from the compact per-splat key array (invalid splats carry
 // 0xffffffff, which no positive depth has); loads are clamped into range and
 // issued unconditionally so that a thread's eight loads overlap.
