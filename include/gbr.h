@@ -77,7 +77,8 @@ typedef struct {
 } gbr_camera;
 
 /* tile: 8, 16 or 32 px.  chunk: 64, 128 or 256 entries staged in LDS per
-   compositing step.  max_*: capacities the context allocates at creation
+   backward compositing step of 32 px tiles (every other compositing takes 64
+   at a time).  max_*: capacities the context allocates at creation
    (frames per call, sum of per-frame Gaussian counts, sum of per-frame pixel
    counts, tile-Gaussian entries).  max_entries grows with gbr_reserve. */
 typedef struct {

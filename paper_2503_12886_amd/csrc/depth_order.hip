@@ -118,9 +118,11 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_count_kernel(PassArgs a
 __global__ __launch_bounds__(kBucketThreads) void bucket_scatter_kernel(PassArgs a) {
   __shared__ uint32_t hist[kMaxBuckets / kBucketParts];
   __shared__ uint32_t red[2 * (kBucketThreads / 64)];
-  const int b = blockIdx.y, blk = blockIdx.x / kBucketParts;
+  int b, part;
+  if (!frame_block(a, a.nblk * kBucketParts, b, part)) return;
+  const int blk = part / kBucketParts;
   const int per = a.nbk / kBucketParts;
-  const uint32_t lo = (uint32_t)((blockIdx.x % kBucketParts) * per);
+  const uint32_t lo = (uint32_t)((part % kBucketParts) * per);
   const FrameDev& F = a.frames[b];
   if ((int64_t)blk * kBucketBlock >= F.gauss_count) return;
   // the keys and this block's offsets in its buckets are read first: neither
@@ -318,7 +320,7 @@ void launch_depth_order(const PassArgs& a, int64_t max_frame_splats, const ScanJ
   const int64_t nb = (int64_t)a.B * a.nbk;
   hipLaunchKernelGGL(bucket_count_kernel, grid, dim3(kBucketThreads), 0, s, a);
   launch_bucket_scan(a, side, s);
-  hipLaunchKernelGGL(bucket_scatter_kernel, grid, dim3(kBucketThreads), 0, s, a);
+  hipLaunchKernelGGL(bucket_scatter_kernel, frame_grid(a, a.nblk * kBucketParts), dim3(kBucketThreads), 0, s, a);
   const int ns = std::min(div_up(nb, kOrderThreads), 512);   // large-bucket workgroups: 256 buckets each at most
   hipLaunchKernelGGL(bucket_order_kernel, dim3(ns + div_up(nb, kRankBuckets)), dim3(kOrderThreads), 0, s, a, ns);
 }

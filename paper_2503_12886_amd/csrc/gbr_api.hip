@@ -130,7 +130,7 @@ struct gbr_ctx {
   unsigned long long *bkeys = nullptr, *bkeys_alt = nullptr;
   uint32_t *depth_sorted = nullptr, *hits = nullptr;
   int64_t cap_bkt = 0, cap_bkt_cells = 0;
-  int nbk = 64, nblk = 1;
+  int nbk = 64, nblk = 1, by_xcd = 0;
   float* part = nullptr;
   uint32_t* n_iter = nullptr;
   uint32_t* n_contrib = nullptr;
@@ -221,6 +221,7 @@ PassArgs make_args(gbr_ctx* c) {
   a.seg_words = c->seg_words;
   a.seg_stride = a.bitmap_words / a.seg_words;
   a.seg_cnt = c->seg_cnt;
+  a.by_xcd = c->by_xcd;
   a.blk_mm = c->blk_mm; a.bkt_count = c->bkt_count; a.bkt_moff = c->bkt_moff; a.bkt_start = c->bkt_start;
   a.bkeys = c->bkeys; a.bkeys_alt = c->bkeys_alt; a.depth_sorted = c->depth_sorted; a.hits = c->hits;
   a.n_iter = c->n_iter; a.n_contrib = c->n_contrib; a.t_final = c->t_final; a.part = c->part;
@@ -502,6 +503,13 @@ int set_pass(gbr_ctx* c, const float* raw, const int64_t* goff, const gbr_camera
   c->B = B; c->n_tiles = nt; c->n_pixels = np; c->n_splats = ns; c->max_frame_splats = mfs;
   c->nbk = nbk;
   c->nblk = nblk;
+  // frames on XCDs of their own only where that leaves the XCDs evenly filled,
+  // frames of about one size and their number close to a multiple of 8: of 50k
+  // splats each, scatter pass / bitmap rows without and with it (us): 8 frames
+  // 9.4 / 20.0 and 8.3 / 17.1, 14 12.1 / 28.6 and 10.5 / 28.0, but 12 11.6 / 26.9
+  // and 10.1 / 27.4, 10 (60k) 10.1 / 26.3 and 10.0 / 31.5, one 7.7 / 9.1 and 7.7 /
+  // 15.8, 8 of 20k to 100k 10.2 / 21.5 and 9.7 / 27.4
+  c->by_xcd = B >= 8 && (B + 7) / 8 * 8 * 7 <= B * 8 && 10 * ns >= 9 * mfs * B ? 1 : 0;
   c->seg_words = seg_words;
   c->max_frame_tiles = mft;
   return GBR_OK;

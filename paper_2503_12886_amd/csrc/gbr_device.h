@@ -6,6 +6,23 @@
 
 namespace gbr {
 
+// The workgroup's frame and its place among the frame's `per` in a grid of
+// frame_grid(a, per); false: no frame.  With by_xcd, frame b's workgroups are those whose
+// index is b mod 8, so that they run on one XCD: the keys that a frame's
+// blocks scatter, and the splats' rectangles that are gathered in depth order,
+// stay in its L2 instead of passing through all eight.  64 frames of 100k
+// splats: scatter pass 80 -> 43 us, bitmap rows 153 -> 149; 16 of 50k: 13 -> 10,
+// 31 -> 27.  (The ranking gains nothing: 42 -> 45.)
+__device__ __forceinline__ bool frame_block(const PassArgs& a, int per, int& b, int& blk) {
+  b = blockIdx.y;
+  blk = blockIdx.x;
+  if (!a.by_xcd) return true;
+  const int i = blk / 8;
+  b = i / per * 8 + blk % 8;
+  blk = i % per;
+  return b < a.B;
+}
+
 // Inclusive scan across the wave by DPP adds: four shifts inside the rows of
 // 16 lanes, then the rows' totals carried on (lane 15 of rows 0 and 2 into
 // rows 1 and 3, lane 31 into rows 2 and 3).  Six VALU adds; by lane shuffles

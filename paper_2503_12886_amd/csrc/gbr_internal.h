@@ -98,6 +98,7 @@ struct PassArgs {
   // per-frame depth order
   int32_t nbk;              // depth buckets per frame
   int32_t nblk;             // workgroups of kBucketBlock splats per frame in the bucket passes
+  int32_t by_xcd;           // the depth and binning passes keep a frame's workgroups on one XCD (frame_block)
   int32_t bitmap_words;     // words per tile bitmap row (largest frame's splats / 32, rounded up to 16)
   int32_t seg_words;        // words per row segment (8 or 16); a segment's set bits are counted once
   int32_t seg_stride;       // segments per row = bitmap_words / seg_words
@@ -274,6 +275,10 @@ void launch_blend_bwd(const float* draw, const float* bases, const float* weight
 int64_t blend_bwd_partials(int B, int K, int64_t N);
 // an upper bound of the floats of partials launch_blend_bwd writes and reads for this shape
 int64_t blend_bwd_partials_used(int B, int K, int64_t N);
+// The grid of `per` workgroups a frame (frame_block).
+inline dim3 frame_grid(const PassArgs& a, int per) {
+  return a.by_xcd ? dim3((unsigned)per * ((a.B + 7) / 8 * 8)) : dim3(per, a.B);
+}
 // Exclusive scan of in[0, n) into out[0, n] (out[n] = total).  The grand total
 // is stored to total_out when non-null, and sets the overflow flag when it
 // exceeds cap_check (>= 0).  block_sums holds scan_scratch_words(n) words.

@@ -390,15 +390,16 @@ int bitmap_seg_words(int max_frame_tiles, int64_t row_words) {
 }
 
 template <int SW>
-__global__ __launch_bounds__(32 * SW) void bitmap_rows_kernel(PassArgs a) {
+__global__ __launch_bounds__(32 * SW) void bitmap_rows_kernel(PassArgs a, int per) {
   constexpr int NT = 32 * SW;                 // one thread per rank of the segment
   constexpr int ST = SW + 1;                  // LDS words per tile
   __shared__ __align__(16) uint32_t words[kRowBuildWords];
-  const int b = blockIdx.y;
+  int b, seg;
+  if (!frame_block(a, per, b, seg)) return;
   const FrameDev& F = a.frames[b];
   const uint32_t vbase = a.bkt_start[b * a.nbk];
   const uint32_t nv = a.bkt_start[(b + 1) * a.nbk] - vbase;
-  const uint32_t r0 = blockIdx.x * (uint32_t)NT;
+  const uint32_t r0 = seg * (uint32_t)NT;
   if (r0 >= nv || a.status->overflow) return;
   const int nw4 = F.n_tiles * (SW / 4);
   const int nz4 = (F.n_tiles * ST + 3) / 4;   // <= kRowBuildWords / 4 (a multiple of 4 words)
@@ -416,7 +417,6 @@ __global__ __launch_bounds__(32 * SW) void bitmap_rows_kernel(PassArgs a) {
   }
   __syncthreads();
   // every tile's bit count, also kept in its segment's pad word
-  const int seg = (int)blockIdx.x;
   uint16_t* cnt = a.seg_cnt + (int64_t)F.tile_base * a.seg_stride + seg;
   for (int t = threadIdx.x; t < F.n_tiles; t += NT) {
     uint32_t c = 0;
@@ -469,12 +469,13 @@ __global__ __launch_bounds__(256) void seg_count_kernel(PassArgs a) {
 void launch_bitmap_rows(const PassArgs& a, int64_t max_frame_splats, int max_frame_tiles, hipStream_t s) {
   if (a.B == 0 || max_frame_splats == 0) return;
   const bool in_lds = (int64_t)max_frame_tiles * (a.seg_words + 1) <= kRowBuildWords;
+  const int per = (int)div_up(max_frame_splats, 32 * a.seg_words);
   if (in_lds && a.seg_words == 32) {
-    hipLaunchKernelGGL(bitmap_rows_kernel<32>, dim3(div_up(max_frame_splats, 1024), a.B), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(bitmap_rows_kernel<32>, frame_grid(a, per), dim3(1024), 0, s, a, per);
   } else if (in_lds && a.seg_words == 16) {
-    hipLaunchKernelGGL(bitmap_rows_kernel<16>, dim3(div_up(max_frame_splats, 512), a.B), dim3(512), 0, s, a);
+    hipLaunchKernelGGL(bitmap_rows_kernel<16>, frame_grid(a, per), dim3(512), 0, s, a, per);
   } else if (in_lds && a.seg_words == 8) {
-    hipLaunchKernelGGL(bitmap_rows_kernel<8>, dim3(div_up(max_frame_splats, 256), a.B), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(bitmap_rows_kernel<8>, frame_grid(a, per), dim3(256), 0, s, a, per);
   } else {
     launch_fill_u32(a.tbits, 0u, (int64_t)a.n_tiles * a.bitmap_words, s);
     hipLaunchKernelGGL(bitmap_rows_atomic_kernel, dim3(div_up(max_frame_splats, 256), a.B), dim3(256), 0, s, a);

@@ -13,7 +13,8 @@ from test_gpu_list_stream import faint_pile
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("sizes", [[1], [8191, 40], [8192], [3, 8193, 700], [16385, 1, 8192, 20000, 511, 513]])
+@pytest.mark.parametrize("sizes", [[1], [8191, 40], [8192], [3, 8193, 700], [16385, 1, 8192, 20000, 511, 513],
+                                   [8193] * 8, [600] * 14, [100] * 15 + [99]])    # (frames on XCDs of their own)
 @pytest.mark.parametrize("spread", ["even", "clustered"])
 def test_order(sizes, spread):
     rng = np.random.default_rng(sum(sizes))
