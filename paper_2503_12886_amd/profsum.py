@@ -40,8 +40,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # source files whose change invalidates a kernel's measured traffic
 KERNEL_SOURCES = {
-    "composite_bwd": ["paper_2503_12886_amd/csrc/raster_bwd.hip", "paper_2503_12886_amd/csrc/gbr_internal.h"],
-    "composite_fwd": ["paper_2503_12886_amd/csrc/raster_fwd.hip", "paper_2503_12886_amd/csrc/gbr_internal.h"],
+    k: [f"paper_2503_12886_amd/csrc/{f}" for f in (src, "gbr_device.h", "gbr_internal.h")]
+    for k, src in (("composite_bwd", "raster_bwd.hip"), ("composite_fwd", "raster_fwd.hip"))
 }
 
 
