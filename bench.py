@@ -323,7 +323,7 @@ def kernel_roofline(ms: dict, cfg, X: int, P: int, P_hit: int, visible: int, ste
     work = {   # group: (bound, amount, what)
         "blend": ("hbm", (K + 1) * N * G + B * N * G, "bases read, blended Gaussians written"),
         "preprocess": ("hbm", B * N * (G + 48), "blended Gaussians read, 48-B splat records written"),
-        "depth_order": ("hbm", visible * 24, "24 B per visible splat (key read, rank written, order written)"),
+        "depth_order": ("hbm", visible * 24, "24 B per visible splat (key read, grouped keys written and read, order written)"),
         "binning": ("hbm", P * 4 + B * N * 8, "each tile entry emitted once (4 B), per-splat count and offset"),
         "tile_scan": ("hbm", n_tiles * 8, "per-tile count read, start written"),
         "tile_sort": ("hbm", n_tiles * 8, "per-tile work read, schedule written"),
