@@ -571,11 +571,23 @@ __global__ __launch_bounds__(kScanThreads) void tile_totals_classify_kernel(Scan
   else classify_block<kScanThreads>(a, (int)blockIdx.x - nb0, false, cnt, base);
 }
 
+// The same for fewer than kScanBlock tiles, whose scan is one block's: both in
+// a launch, 3.5 + 3.0 -> 3.2 us for 1024 tiles, 4.5 + 4.8 -> 4.8 for 3360.
+__global__ __launch_bounds__(kScanThreads) void tile_scan_classify_kernel(ScanJob J, PassArgs a) {
+  __shared__ uint32_t cnt[33], base[33];
+  if (blockIdx.x == 0) scan_apply_block(J, 0, a.status);
+  else classify_block<kScanThreads>(a, (int)blockIdx.x - 1, false, cnt, base);
+}
+
 void launch_tile_scan_classify(const PassArgs& a, uint32_t* block_sums, int64_t cap_check,
                                unsigned long long* total_out, hipStream_t s) {
   const ScanJob J{a.tile_count, a.tile_start, a.n_tiles, block_sums, cap_check, total_out};
   const int nb0 = (int)div_up((int64_t)a.n_tiles + 1, kScanBlock);
   const int ncls = a.n_tiles > 0 ? div_up(a.n_tiles, 1024) : 0;
+  if (nb0 == 1) {                             // one block: no totals to wait for
+    hipLaunchKernelGGL(tile_scan_classify_kernel, dim3(1 + ncls), dim3(kScanThreads), 0, s, J, a);
+    return;
+  }
   hipLaunchKernelGGL(tile_totals_classify_kernel, dim3(nb0 + ncls), dim3(kScanThreads), 0, s, J, nb0, a);
   hipLaunchKernelGGL(scan_apply_kernel, dim3(nb0), dim3(kScanThreads), 0, s, J, a.status);
 }
