@@ -393,13 +393,20 @@ int stage_and_upload(gbr_ctx* c, hipStream_t s) {
 }
 
 int enqueue_preprocess(gbr_ctx* c, const float* raw, hipStream_t s) {
-  int rc = stage_and_upload(c, s);
-  if (rc) return rc;
+  // a captured pass reads the table that its replays upload; a few frames of an
+  // eager one go with the projection's arguments
+  const bool by_args = !c->capturing && c->B <= kArgFrames && c->max_frame_splats > 0;
+  if (by_args) {
+    c->frames_replay_ready = false;   // the device table is this pass's now
+  } else {
+    int rc = stage_and_upload(c, s);
+    if (rc) return rc;
+  }
   PassArgs a = make_args(c);
   bool projected;
   {
     KTimer t(c, GBR_K_PREPROCESS, s);
-    projected = launch_preprocess(a, raw, c->max_frame_splats, s);   // also clears the pass's counters
+    projected = launch_preprocess(a, by_args ? c->frames_host.data() : nullptr, raw, c->max_frame_splats, s);   // also clears the pass's counters
   }
   if (!projected) hipLaunchKernelGGL(begin_pass_kernel, dim3(1), dim3(256), 0, s, a);
   c->cls_clean = true;

@@ -296,7 +296,14 @@ void launch_bucket_scan(const PassArgs& a, const ScanJob& side, hipStream_t s);
 int64_t scan_scratch_words(int64_t n);
 // Returns whether it launched (no frame has Gaussians otherwise): the
 // launch also clears the pass's counters.
-bool launch_preprocess(const PassArgs& a, const float* raw, int64_t max_frame_splats, hipStream_t s);
+// host_frames: null when the frame table is in device memory, else the host's
+// (at most kArgFrames frames), which the projection takes as an argument and
+// stores: the copy and its event before every eager pass cost a frame of 50k
+// Gaussians 6 us of 164, five of 30k (render and backward) 4 of 263.  More frames
+// would not fit a kernel's arguments beside the rest.
+constexpr int kArgFrames = 16;
+bool launch_preprocess(const PassArgs& a, const FrameDev* host_frames, const float* raw, int64_t max_frame_splats,
+                       hipStream_t s);
 // Words per bitmap row segment for frames of up to max_frame_tiles tiles
 // (the workgroup that builds a segment of every row of a frame holds them in LDS).
 constexpr int kMaxRowSegs = 1024;   // segments per bitmap row at most (the compositing lists them in LDS)

@@ -294,12 +294,30 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return v;
 }
 
-__global__ __launch_bounds__(256) void preprocess_kernel(PassArgs a, const float* __restrict__ raw) {
+// The pass's frames: in device memory already, or in the kernel's arguments,
+// from where the first workgroup stores them for the kernels that follow.
+struct StoredFrames {
+  __device__ __forceinline__ const FrameDev& at(const PassArgs& a, int b) const { return a.frames[b]; }
+  __device__ __forceinline__ void store(const PassArgs&) const {}
+};
+struct ArgFrames {
+  FrameDev f[kArgFrames];
+  __device__ __forceinline__ const FrameDev& at(const PassArgs&, int b) const { return f[b]; }
+  __device__ __forceinline__ void store(const PassArgs& a) const {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(f);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(const_cast<FrameDev*>(a.frames));
+    for (int i = threadIdx.x; i < a.B * (int)(sizeof(FrameDev) / 4); i += 256) dst[i] = src[i];
+  }
+};
+
+template <typename Frames>
+__global__ __launch_bounds__(256) void preprocess_kernel(PassArgs a, Frames frames, const float* __restrict__ raw) {
   __shared__ uint32_t wmin[4], wmax[4];
   const int b = blockIdx.y;
-  const FrameDev& F = a.frames[b];
+  const FrameDev& F = frames.at(a, b);
   const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (blockIdx.x == 0 && b == 0) {   // the pass's counters: this is its first kernel
+    frames.store(a);
     if (threadIdx.x < 66) a.cls_cnt[threadIdx.x] = 0u;
     if (threadIdx.x == 0) { a.status->overflow = 0u; a.status->entries = 0ull; }
   }
@@ -351,9 +369,17 @@ __global__ __launch_bounds__(256) void preprocess_kernel(PassArgs a, const float
   }
 }
 
-bool launch_preprocess(const PassArgs& a, const float* raw, int64_t max_frame_splats, hipStream_t s) {
+bool launch_preprocess(const PassArgs& a, const FrameDev* host_frames, const float* raw, int64_t max_frame_splats,
+                       hipStream_t s) {
   if (a.B == 0 || max_frame_splats == 0) return false;
-  hipLaunchKernelGGL(preprocess_kernel, dim3(div_up(max_frame_splats, 256), a.B), dim3(256), 0, s, a, raw);
+  const dim3 grid(div_up(max_frame_splats, 256), a.B);
+  if (host_frames) {
+    ArgFrames f;
+    for (int b = 0; b < kArgFrames; ++b) f.f[b] = host_frames[b < a.B ? b : 0];
+    hipLaunchKernelGGL(preprocess_kernel<ArgFrames>, grid, dim3(256), 0, s, a, f, raw);
+  } else {
+    hipLaunchKernelGGL(preprocess_kernel<StoredFrames>, grid, dim3(256), 0, s, a, StoredFrames(), raw);
+  }
   return true;
 }
 
