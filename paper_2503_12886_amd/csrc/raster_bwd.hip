@@ -303,17 +303,20 @@ __global__ __launch_bounds__(TileShapeB<32>::NT) void composite_bwd32_kernel(Pas
 // contributing pixel in the wave and its partial is written unchecked.
 //
 // Per visited entry a lane forms two numbers, t and the blending weight; the
-// entry's nine sums over the pixels are their products with quantities that
-// belong to the pixel alone: t with 1, x, y, x^2, xy, y^2 (x, y from the
-// quadrant's centre) and the weight with the pixel's three image gradients.
-// So the sums are taken 8 entries at a time with the roles of the lanes
-// exchanged: the two numbers go to LDS a row of 64 pixels per entry, and lane
-// 8 e + y reads back the 8 pixels of row y of entry e, sums them along x in
-// registers (the powers of x are literals, the image gradients of its 8
-// pixels stay in registers), forms the y moments of its sums, and 20 more
-// operations add the 8 lanes' nine sums: 9 vector operations a visit where
-// nine products and the cross-lane sums of each entry took 27.  The moments
-// about the mean follow from those about the centre once per (tile, entry).
+// entry's nine sums over the pixels are t's products with 1, dx, dy, dx^2,
+// dx dy, dy^2 (the pixel's offset from the mean) and the weight's with the
+// pixel's three image gradients.  The sums are taken 8 entries at a time with
+// the roles of the lanes exchanged: the two numbers go to LDS a row of 64
+// pixels per entry, and lane 8 e + y reads back the 8 pixels of row y of entry
+// e, sums them along x in registers (dx from the entry's mean; the image
+// gradients of its 8 pixels stay in registers), forms the y moments of its
+// sums (dy is one number for the row), and 20 more operations add the 8 lanes'
+// nine sums: 12 vector operations a visit where nine products and the
+// cross-lane sums of each entry took 27.  (Moments about the quadrant's
+// centre, moved to the mean once per (tile, entry), take 9 operations, the powers
+// of x being literals, but the move cancels where the splat is smaller than its
+// distance from the centre: for the smallest splats, sigma 0.55 pixels, the
+// second moments carry 80 u sum |t| dx^2 where these carry 0.6.)
 // (As a product on the matrix cores, 16 v_mfma_f32_16x16x4f32 per 8 entries,
 // the sums cost as much: 6 and 3 of its 16 columns are used, and the vector
 // unit stands still meanwhile.)
@@ -429,9 +432,14 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
     // <colour behind the current entry, dL/dout>, starts at <T_end * background, dL/dout>
     SG = T_ * (F.bg[0] * G0 + F.bg[1] * G1 + F.bg[2] * G2);
   }
-  // the lane's part of the sums: row oy (from the quadrant's centre) of entry
-  // lane / 8 of a group; the image gradients of that row's pixels
-  const float oy = (float)(lane & 7) - 3.5f;
+  // the lane's part of the sums: a row of entry lane / 8 of a group, its pixel
+  // centres at (qx[k], qy); the image gradients of that row's pixels
+  const int q0x = tx * T + (w & 1) * 8, q0y = ty * T + (w >> 1) * 8;   // (w = 0 in tiles of 8)
+  const float qy = (float)(q0y + (lane & 7)) + 0.5f;
+  float qx[8];                              // (uniform: scalar registers)
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    qx[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)(q0x + k) + 0.5f)));
   float* tw = tb[w];
   const float* twr = tw + (lane >> 3) * kBwdRow + (lane & 7) * 4;
   const int cell = (lane & 4) * 8 + (lane >> 3) * 4 + (lane & 3);
@@ -449,7 +457,6 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
   }
   // this lane's part of a batch's write-out: a quadrant's sums of one entry
   const int oi = w * (64 / NW) + lane / NW, oq = lane % NW;
-  const float ocx = (float)(tx * T + (oq & 1) * 8) + 4.0f, ocy = (float)(ty * T + (oq >> 1) * 8) + 4.0f;
   const uint32_t oql = a.qlast[g * 4 + oq];   // quadrant oq took nothing at or past it (its masks end there)
   const unsigned long long* qmask = a.qmask + 4 * ((int64_t)(start >> 6) + g) + oq;
   const uint32_t* srt = a.sorted + start;
@@ -494,7 +501,6 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
       x |= __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, false);
       any = x != 0;
     }
-    const float omx = st[0][oi].x - ocx, omy = st[0][oi].y - ocy;
     const uint32_t oslot = slot[oi];
     // ---- the quadrant's entries, back to front, in groups of 8 ----
     while (m) {
@@ -523,6 +529,8 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
       }
       wave_sync();
       // the row's 8 pixels (a short group's unwritten rows only spoil their own sums)
+      const uint32_t e = ((lane & 32 ? ehi : elo) >> (lane & 24)) & 0xffu;
+      const float2 mean = *reinterpret_cast<const float2*>(&st[0][e]);
       float t[8], wg[8];
 #pragma unroll
       for (int k = 0; k < 8; k += 4) {
@@ -535,21 +543,20 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
       wave_sync();
       float v[9];
       {
-        float sm[4], df[4];
+        float p[8], m2 = 0.0f;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { sm[k] = t[7 - k] + t[k]; df[k] = t[7 - k] - t[k]; }
-        v[5] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
-        v[0] = 3.5f * df[0];
-        v[2] = 12.25f * sm[0];
-#pragma unroll
-        for (int k = 1; k < 4; ++k) {
-          const float x = 3.5f - (float)k;
-          v[0] = __builtin_fmaf(x, df[k], v[0]);
-          v[2] = __builtin_fmaf(x * x, sm[k], v[2]);
+        for (int k = 0; k < 8; ++k) {
+          const float dx = qx[k] - mean.x;
+          p[k] = t[k] * dx;
+          m2 = k == 0 ? p[0] * dx : __builtin_fmaf(p[k], dx, m2);
         }
-        v[1] = oy * v[5];
-        v[3] = oy * v[0];
-        v[4] = oy * v[1];
+        const float dy = qy - mean.y;
+        v[5] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+        v[0] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        v[2] = m2;
+        v[1] = dy * v[5];
+        v[3] = dy * v[0];
+        v[4] = dy * v[1];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           v[6 + c] = wg[0] * gx[0][c];
@@ -559,22 +566,15 @@ __global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(Pas
       }
       float ninth;
       const float tot = octets_transposed9(v, lane, ninth);
-      const uint32_t e = ((lane & 32 ? ehi : elo) >> (lane & 24)) & 0xffu;
       red[e][w][value] = tot;
       if ((lane & 7) == 0) red[e][w][8] = ninth;
     }
     __syncthreads();
-    // ---- the batch's partials: the quadrants' sums, moved to the mean, added in order ----
+    // ---- the batch's partials: the quadrants' sums added in order ----
     if (any) {
       float v[9];
 #pragma unroll
       for (int c = 0; c < 9; ++c) v[c] = obit ? red[oi][oq][c] : 0.0f;
-      const float m1x = v[0], m1y = v[1];
-      v[0] = __builtin_fmaf(-omx, v[5], m1x);
-      v[1] = __builtin_fmaf(-omy, v[5], m1y);
-      v[2] = __builtin_fmaf(-omx, v[0], __builtin_fmaf(-omx, m1x, v[2]));
-      v[3] = __builtin_fmaf(-omx, v[1], __builtin_fmaf(-omy, m1x, v[3]));
-      v[4] = __builtin_fmaf(-omy, v[1], __builtin_fmaf(-omy, m1y, v[4]));
       if (NW == 4) {                        // (an entry's four lanes take this branch together)
 #pragma unroll
         for (int c = 0; c < 9; ++c) {
