@@ -342,12 +342,13 @@ constexpr int kBwdRow = 64;
 // One entry folded into a lane's back-to-front state (transmittance in front
 // of the entry, colour behind it), in two parts.  A lane whose pixel did not
 // take the entry folds alpha / (1 - alpha) = 0: its state passes through
-// unchanged and t and the weight are 0.  (Where rounding makes the
+// unchanged, the weight is 0 and so is t, whatever the state (a product in which
+// 0 times anything is 0, or a gradient that is not finite at this pixel would
+// reach entries that it did not take).  (Where rounding makes the
 // clamped quadratic form negative, at a pixel on the mean, the power's
 // gradient passes as it does without the rounding.)
 struct EntryAlpha {
-  float q, cg;           // alpha / (1 - alpha), <colour, dL/dout>
-  bool below;            // not clamped
+  float q, qt, cg;       // alpha / (1 - alpha), the same with 0 where the alpha is clamped, <colour, dL/dout>
 };
 __device__ __forceinline__ EntryAlpha entry_alpha(float al, bool before_stop, const float4 r1, float cbl, float G0,
                                                   float G1, float G2) {
@@ -355,7 +356,7 @@ __device__ __forceinline__ EntryAlpha entry_alpha(float al, bool before_stop, co
   const float q = al * __builtin_amdgcn_rcpf(1.0f - al);
   x.q = before_stop && al >= kAlphaMin ? q : 0.0f;
   x.cg = r1.z * G0 + r1.w * G1 + cbl * G2;
-  x.below = al < kAlphaMax;                         // min(0.99, .) passes the gradient only below the clamp
+  x.qt = al < kAlphaMax ? x.q : 0.0f;               // min(0.99, .) passes the gradient only below the clamp
   return x;
 }
 __device__ __forceinline__ void entry_fold(const EntryAlpha& x, float& T_, float& SG, float& t, float& wgt) {
@@ -363,7 +364,7 @@ __device__ __forceinline__ void entry_fold(const EntryAlpha& x, float& T_, float
   wgt = x.q * T_;                                   // alpha times the transmittance in front of the entry
   SG += wgt * x.cg;                                 // <colour behind, dL/dout>
   T_ += wgt;
-  t = x.below ? x.q * d : 0.0f;
+  asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(t) : "v"(x.qt), "v"(d));   // q d, 0 for q = 0
 }
 
 // The highest set bit of a wave-uniform mask, cleared there (64: none).
