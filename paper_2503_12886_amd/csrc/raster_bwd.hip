@@ -14,15 +14,13 @@ template <int T> using TileShapeB = TileMap<T>;
 // The clamp is one v_min_f32 (min(power, lo) for every non-NaN power);
 // written as such because fminf would first canonicalise lo, one more
 // instruction per (entry, pixel).
-__device__ __forceinline__ float splat_alpha_b(float4 r0, float4 r1, float px, float py, float& dx, float& dy,
-                                               float& pw_raw) {
+__device__ __forceinline__ float splat_alpha_b(float4 r0, float4 r1, float px, float py, float& dx, float& dy) {
 #pragma clang fp contract(off)
   dx = px - r0.x;
   dy = py - r0.y;
   float pw = __builtin_fmaf(r0.z * dx, dx, r1.y);
   pw = __builtin_fmaf(r0.w * dx, dy, pw);
   pw = __builtin_fmaf(r1.x * dy, dy, pw);
-  pw_raw = pw;
   float pc;
   asm("v_min_f32 %0, %1, %2" : "=v"(pc) : "v"(pw), "v"(r1.y));
   return __builtin_amdgcn_exp2f(pc);
@@ -38,6 +36,12 @@ __device__ __forceinline__ float splat_alpha_b(float4 r0, float4 r1, float px, f
 // 2 cc) times the first moments, the opacity logit (1 - o) sum t.  Along the
 // traversal each lane keeps only the transmittance and <colour behind,
 // dL/dout>.
+// The power passes its gradient also where rounding lifts it above log2 o and
+// it is clamped there: the quadratic form is never negative, so the clamp
+// removes an error and no dependence.  (With no gradient from those pixels,
+// splats thousands of pixels long, whose conic is indefinite in binary32, had
+// 1 to 20 % of the terms' magnitude wrong in the long scale's gradient, and
+// 0.1 % with it.)
 // A wave's sum over its lanes is taken in a fixed order; the block then adds
 // its waves in order and writes the entry's partial, by emission slot, only
 // if some pixel contributed; a byte flag marks it.
@@ -52,8 +56,8 @@ __device__ __forceinline__ void entry_grad(const float4 r0, const float4 r1, con
                                            float* acc) {
 #pragma unroll
   for (int p = 0; p < PX; ++p) {
-    float dx, dy, pwr;
-    const float a0 = splat_alpha_b(r0, r1, pxf[p], pyf[p], dx, dy, pwr);
+    float dx, dy;
+    const float a0 = splat_alpha_b(r0, r1, pxf[p], pyf[p], dx, dy);
     const bool take = li < nit[p] && a0 >= kAlphaMin;
     // an untaken entry folds with alpha 0: 1/(1 - 0) = 1 exactly, so the
     // transmittance passes through unchanged and the weight is 0
@@ -67,9 +71,7 @@ __device__ __forceinline__ void entry_grad(const float4 r0, const float4 r1, con
     T_[p] = Ti;
     // min(0.99, .) passes the gradient only below the clamp
     const float t = (take && a0 < kAlphaMax) ? a0 * dal : 0.0f;
-    // power clamped at log2 o (q < 0 by rounding): no gradient to the conic or mean
-    const float tq = (pwr > r1.y) ? 0.0f : t;
-    const float p1 = tq * dx, p2 = tq * dy;
+    const float p1 = t * dx, p2 = t * dy;
     const float v[9] = {p1, p2, p1 * dx, p1 * dy, p2 * dy, t, wgt * G0[p], wgt * G1[p], wgt * G2[p]};
     // the first pixel assigns (adding it to 0 would cost an instruction per value)
 #pragma unroll
@@ -344,9 +346,7 @@ constexpr int kBwdRow = 64;
 // take the entry folds alpha / (1 - alpha) = 0: its state passes through
 // unchanged, the weight is 0 and so is t, whatever the state (a product in which
 // 0 times anything is 0, or a gradient that is not finite at this pixel would
-// reach entries that it did not take).  (Where rounding makes the
-// clamped quadratic form negative, at a pixel on the mean, the power's
-// gradient passes as it does without the rounding.)
+// reach entries that it did not take).
 struct EntryAlpha {
   float q, qt, cg;       // alpha / (1 - alpha), the same with 0 where the alpha is clamped, <colour, dL/dout>
 };
