@@ -278,7 +278,8 @@ int gbr_loss(gbr_ctx* ctx, const float* images, const float* targets, int32_t ki
 int gbr_mlp_forward(gbr_ctx* ctx, const float* params, const float* theta, int32_t B, int32_t d_in, int32_t hidden,
                     int32_t K, float* psi, void* stream);
 /* gbr_mlp_forward and gbr_blend of several models, each with frames and
-   Gaussians of its own, in two launches (per 16 models): psi [B][K] = F(theta
+   Gaussians of its own, in a launch for the MLPs and one for the blends (more
+   where the models' K differ much), per 16 models: psi [B][K] = F(theta
    [B][d_in]), raw [B][N][16] blended from bases [(K+1)][N][16], with the bits
    of the two calls.  Keeps no activations.  1 <= K <= 63, else the limits of
    both; the groups' psi and raw must not overlap. */

@@ -99,10 +99,42 @@ __global__ __launch_bounds__(kBlendThreads) void blend_drive_kernel(DriveTable t
 
 int64_t blend_drive_blocks(int64_t N) { return div_up(N * kNF, kBlendThreads); }
 
-void launch_blend_drive(const DriveTable& t, int max_K, hipStream_t s) {
-  with_slices(max_K, [&](auto km) {
-    hipLaunchKernelGGL(blend_drive_kernel<km()>, dim3(t.blocks), dim3(kBlendThreads), 0, s, t);
-  });
+// Models of one instance (slices in eights) share a launch, and those of fewer
+// slices join it while the slices they would read and multiply for nothing cost
+// less than a launch of their own: some 0.3 to 0.45 ns a workgroup and eight
+// slices against 4 us.  8 models' MLPs and blends (us, in one launch / as here):
+// K = 20 and one of 63, 60k Gaussians 220 / 164, 20k 82 / 59, 2k 18 / 18; K = 7,
+// 15, ... 63, 60k 245 / 217, 20k 93 / 86, 2k 19 / 19 (43 in eight); K = 20 and 25
+// in turn, 60k 144 / 147, 20k 47 / 47 (52 in two).
+constexpr int64_t kDriveWaste = 12000;
+
+void launch_blend_drive(const DriveTable& t, hipStream_t s) {
+  int64_t blocks8[kBlendW64Stride / 8] = {};   // workgroups per instance
+  for (int i = 0; i < t.groups; ++i) blocks8[t.g[i].K / 8] += blend_drive_blocks(t.g[i].N);
+  for (int hi = kBlendW64Stride / 8 - 1; hi >= 0;) {
+    int lo = hi;                        // the launch takes instances [lo, hi]
+    if (blocks8[hi] > 0)
+      for (int64_t waste = 0; lo > 0 && (waste += blocks8[lo - 1] * (hi - lo + 1)) <= kDriveWaste;) --lo;
+    DriveTable u;                       // (block0 alone is searched: frame0 keeps the weight rows)
+    int n = 0;
+    u.blocks = 0;
+    for (int i = 0; i < t.groups; ++i) {
+      const int k8 = t.g[i].K / 8;
+      if (k8 < lo || k8 > hi) continue;
+      u.g[n] = t.g[i];
+      u.frame0[n] = t.frame0[i];
+      u.block0[n] = u.blocks;
+      u.blocks += (uint32_t)blend_drive_blocks(t.g[i].N);
+      ++n;
+    }
+    if (n > 0) {
+      u.close(n, t.frames, t.w64);
+      with_slices(8 * hi, [&](auto km) {
+        hipLaunchKernelGGL(blend_drive_kernel<km()>, dim3(u.blocks), dim3(kBlendThreads), 0, s, u);
+      });
+    }
+    hi = lo - 1;
+  }
 }
 
 void launch_blend_fwd(const float* bases, const float* weights, int B, int K, int64_t N, float* raw, double* w64,

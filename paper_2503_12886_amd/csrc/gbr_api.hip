@@ -1000,7 +1000,7 @@ int gbr_drive(gbr_ctx* c, int32_t n_groups, const gbr_drive_group* groups, int32
     // as many groups as a launch's table, the weight table and a grid hold
     DriveTable t;
     int64_t frames = 0, blocks = 0;
-    int n = 0, max_K = 0;
+    int n = 0;
     for (; n < kDriveGroups && i0 + n < n_groups; ++n) {
       const gbr_drive_group& g = groups[i0 + n];
       const int64_t nb = blend_drive_blocks(g.N);
@@ -1010,22 +1010,16 @@ int gbr_drive(gbr_ctx* c, int32_t n_groups, const gbr_drive_group* groups, int32
       t.block0[n] = (uint32_t)blocks;
       frames += g.B;
       blocks += nb;
-      max_K = std::max(max_K, (int)g.K);
     }
-    for (int k = n; k < kDriveGroups; ++k) {
-      t.g[k] = DriveGroup{};
-      t.frame0[k] = t.block0[k] = 0xffffffffu;
-    }
-    t.frames = (uint32_t)frames;
     t.blocks = (uint32_t)blocks;
-    t.w64 = c->blend_w64;
+    t.close(n, (uint32_t)frames, c->blend_w64);
     {
       KTimer k(c, GBR_K_MLP, (hipStream_t)stream);
       launch_mlp_drive(t, d_in, hidden, (hipStream_t)stream);
     }
     {
       KTimer k(c, GBR_K_BLEND, (hipStream_t)stream);
-      launch_blend_drive(t, max_K, (hipStream_t)stream);
+      launch_blend_drive(t, (hipStream_t)stream);
     }
     GBR_HIP(hipGetLastError());
     i0 += n;

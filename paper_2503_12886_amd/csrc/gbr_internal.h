@@ -256,7 +256,17 @@ struct DriveTable {
   DriveGroup g[kDriveGroups];
   uint32_t frame0[kDriveGroups], block0[kDriveGroups];   // first frame and blend workgroup; 0xffffffff past the last
   uint32_t frames, blocks;
+  int32_t groups;
   double* w64;                                           // [frames][kBlendW64Stride]
+  void close(int n, uint32_t n_frames, double* table) {  // n groups filled
+    groups = n;
+    frames = n_frames;
+    w64 = table;
+    for (int k = n; k < kDriveGroups; ++k) {
+      g[k] = DriveGroup{};
+      frame0[k] = block0[k] = 0xffffffffu;
+    }
+  }
   __device__ __forceinline__ int group_of(const uint32_t (&first)[kDriveGroups], uint32_t x) const {
     int i = 0;
 #pragma unroll
@@ -266,7 +276,7 @@ struct DriveTable {
 };
 int64_t blend_drive_blocks(int64_t N);
 void launch_mlp_drive(const DriveTable& t, int d_in, int hidden, hipStream_t s);
-void launch_blend_drive(const DriveTable& t, int max_K, hipStream_t s);
+void launch_blend_drive(const DriveTable& t, hipStream_t s);
 void launch_blend_fwd(const float* bases, const float* weights, int B, int K, int64_t N, float* raw, double* w64,
                       hipStream_t s);
 void launch_blend_bwd(const float* draw, const float* bases, const float* weights, int B, int K, int64_t N,

@@ -446,7 +446,7 @@ def gbr_mlp_forward(ctx: Context, params, theta, d_in: int, hidden: int, K: int,
 
 
 def gbr_drive(ctx: Context, groups, d_in: int, hidden: int, stream=None) -> None:
-    """gbr_mlp_forward and gbr_blend of several models in two launches: groups
+    """gbr_mlp_forward and gbr_blend of several models in a few launches: groups
     are (mlp, theta [B][d_in], bases [K+1][N][16], psi [B][K], raw [B][N][16]),
     or an array of gbr_drive_group that the caller has filled and checked."""
     if isinstance(groups, ctypes.Array):
