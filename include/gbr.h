@@ -355,10 +355,12 @@ int gbr_graph_end(gbr_ctx* ctx, void* stream, gbr_graph** out);
 int gbr_graph_launch(gbr_graph* g, void* stream);
 int gbr_graph_destroy(gbr_graph* g);
 
-/* Autotuner: renders and back-propagates the given frames once per
-   (tile, chunk) in {8,16,32} x {64,128,256}, times each on `stream`, keeps
-   the fastest in the context and reports it (times_ms: host [9], may be
-   NULL; entries beyond capacity grow it).  Synchronises. */
+/* Autotuner: renders and back-propagates the given frames per (tile, chunk)
+   in {8,16,32} x {64,128,256}, times each on `stream`, keeps the fastest in
+   the context and reports it (times_ms: host [9], may be NULL; entries beyond
+   capacity grow it).  The chunk matters to tiles of 32 alone: those of 8
+   and 16 are timed at 64, and their other chunks get the same time.
+   Synchronises. */
 int gbr_autotune(gbr_ctx* ctx, const float* raw, const int64_t* gauss_offsets, const gbr_camera* cams, int32_t B,
                  float* images_scratch, float* dimages_scratch, float* draw_scratch, void* stream,
                  int32_t* best_tile, int32_t* best_chunk, float* times_ms);

@@ -1207,8 +1207,13 @@ int gbr_autotune(gbr_ctx* c, const float* raw, const int64_t* goff, const gbr_ca
   float best = 1e30f;
   int bt = c->tile, bc = c->chunk;
   int rc = GBR_OK;
-  for (int ti = 0; ti < 3 && !rc; ++ti)
+  for (int ti = 0; ti < 3 && !rc; ++ti) {
+    float ms = 0.f;
     for (int ci = 0; ci < 3 && !rc; ++ci) {
+      if (ci > 0 && tiles[ti] != 32) {   // the chunk makes no difference there: the first one's time
+        if (times_ms) times_ms[ti * 3 + ci] = ms;
+        continue;
+      }
       rc = gbr_set_tiling(c, tiles[ti], chunks[ci]);
       if (rc) break;
       // make sure the entry buffers fit this tile size
@@ -1217,7 +1222,6 @@ int gbr_autotune(gbr_ctx* c, const float* raw, const int64_t* goff, const gbr_ca
       int64_t e = 0;
       rc = gbr_entry_count(c, stream, &e);
       if (rc) break;
-      float ms = 0.f;
       for (int rep = 0; rep < 3 && !rc; ++rep) {
         (void)hipEventRecord(e0, s);
         rc = gbr_render(c, raw, goff, cams, B, images, stream);
@@ -1231,6 +1235,7 @@ int gbr_autotune(gbr_ctx* c, const float* raw, const int64_t* goff, const gbr_ca
       if (times_ms) times_ms[ti * 3 + ci] = ms;
       if (!rc && ms < best) { best = ms; bt = tiles[ti]; bc = chunks[ci]; }
     }
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc) return rc;
