@@ -112,8 +112,8 @@ int gbr_reserve(gbr_ctx* ctx, int64_t max_entries);
 /* Device memory of a context's workspace, in bytes, for callers that budget
    it (the serving executor admits work by the bytes its contexts hold):
    gbr_memory gives what the context holds now (its capacities at creation,
-   grown by gbr_reserve and by the per-pass buffers -- depth buckets, scan
-   scratch, tile bitmap rows -- of the largest pass so far); gbr_plan_bytes
+   grown by gbr_reserve and by the per-pass buffers -- depth buckets, tile
+   bitmap rows -- of the largest pass so far); gbr_plan_bytes
    gives what a context created with cfg would hold after one pass of B
    frames (per-frame Gaussian counts from gauss_offsets, host [B + 1];
    frame sizes widths, heights, host [B]) with at least `entries` tile

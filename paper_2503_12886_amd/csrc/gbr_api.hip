@@ -137,7 +137,6 @@ struct gbr_ctx {
   float* t_final = nullptr;
   uint32_t* scan_scratch = nullptr;
   uint32_t* scan_scratch_splat = nullptr;   // block sums of the per-splat count scan
-  int64_t cap_scan_words = 0;
   float* draw_scratch = nullptr;
   float *ci_ones = nullptr, *ci_draw = nullptr;   // colour initialisation: all-ones images, second adjoint
   float* loss_part = nullptr;
@@ -469,17 +468,6 @@ int set_pass(gbr_ctx* c, const float* raw, const int64_t* goff, const gbr_camera
     rc = alloc_buckets(c, (int64_t)B * nbk, (int64_t)B * nbk * nblk);
     if (rc) return rc;
   }
-  const int64_t scan_words = scan_scratch_words((int64_t)B * nbk * nblk);
-  if (scan_words > c->cap_scan_words) {   // the bucket-count matrix is the longest scan of a pass
-    if (c->capturing) return GBR_ERR_STATE;
-    GBR_HIP(hipDeviceSynchronize());
-    ++c->alloc_gen;
-    dfree(c->scan_scratch);
-    c->cap_scan_words = 0;
-    rc = dalloc(&c->scan_scratch, scan_words);
-    if (rc) return rc;
-    c->cap_scan_words = scan_words;
-  }
   int mft = 0;
   for (const FrameDev& f : fr) mft = std::max(mft, f.n_tiles);
   const int64_t row_words = ((mfs + 31) / 32 + 31) / 32 * 32;
@@ -523,12 +511,12 @@ int set_pass(gbr_ctx* c, const float* raw, const int64_t* goff, const gbr_camera
 }
 
 // Device bytes of a context's workspace from its capacities: the sizes
-// gbr_create allocates, grown by a pass (depth buckets, scan scratch, tile
-// bitmap rows and their segment counts) and by gbr_reserve (entries).  One
+// gbr_create allocates, grown by a pass (depth buckets, tile bitmap rows and
+// their segment counts) and by gbr_reserve (entries).  One
 // formula serves gbr_memory (a context's current bytes) and gbr_plan_bytes
 // (what a context sized for a batch would hold).
 struct WorkspaceCaps {
-  int64_t frames, splats, pixels, tiles, entries, bkt, bkt_cells, scan_words, tbits, seg, ci_pixels, ci_splats;
+  int64_t frames, splats, pixels, tiles, entries, bkt, bkt_cells, tbits, seg, ci_pixels, ci_splats;
   bool timing;
 };
 
@@ -542,7 +530,7 @@ int64_t workspace_bytes(const WorkspaceCaps& k) {
   b += (n(k.splats) * 2) * 8 + n(k.splats) * 4 * 2;                       // bucket keys, order, hits
   b += (n(k.bkt_cells) + n(k.bkt_cells + 1) + n(k.bkt + 1)) * 4;  // depth buckets
   b += 3 * n(k.pixels) * 4;                                                  // n_iter, n_contrib, t_final
-  b += n(k.scan_words) * 4 + n(scan_scratch_words(k.splats)) * 4 + n(k.splats * kNF) * 4;
+  b += n(scan_scratch_words(k.tiles)) * 4 + n(scan_scratch_words(k.splats)) * 4 + n(k.splats * kNF) * 4;
   b += n(2 * loss_partials(3 * k.pixels) + 2) * 4;
   b += n(4 * k.splats + 4096LL * k.frames + 64LL * 64 * 8) * 4;
   b += (int64_t)kBlendMaxFrames * kBlendW64Stride * 8 + 4 * n(k.frames * 1024) * 4;
@@ -558,13 +546,12 @@ int64_t workspace_bytes(const WorkspaceCaps& k) {
 // count and blocks as set_pass chooses them) over n_tiles tiles, the largest
 // frame having max_frame_tiles.
 void pass_caps(int B, int64_t mfs, int64_t n_tiles, int max_frame_tiles, int64_t* bkt, int64_t* cells,
-               int64_t* scan_words, int64_t* tbits, int64_t* seg) {
+               int64_t* tbits, int64_t* seg) {
   int nbk = 64;
   while (nbk < 8192 && (int64_t)nbk * 8 < mfs) nbk *= 2;
   const int64_t nblk = std::max<int64_t>(1, (mfs + kBucketBlock - 1) / kBucketBlock);
   *bkt = (int64_t)B * nbk;
   *cells = (int64_t)B * nbk * nblk;
-  *scan_words = scan_scratch_words(*cells);
   const int64_t row_words = ((mfs + 31) / 32 + 31) / 32 * 32;
   const int sw = bitmap_seg_words(max_frame_tiles, row_words);
   *tbits = std::max<int64_t>(1, n_tiles * row_words);
@@ -581,7 +568,6 @@ WorkspaceCaps caps_at_create(const gbr_config* cfg) {
   k.entries = cfg->max_entries;
   k.bkt = 64LL * cfg->max_frames;
   k.bkt_cells = 64LL * cfg->max_frames;
-  k.scan_words = scan_scratch_words(std::max<int64_t>(std::max<int64_t>(k.splats, k.tiles), 8192LL * k.frames));
   k.tbits = 0;
   k.seg = 0;
   return k;
@@ -647,9 +633,7 @@ int gbr_create(const gbr_config* cfg, gbr_ctx** out) {
   TRY(dalloc(&c->n_iter, c->cap_pixels));
   TRY(dalloc(&c->n_contrib, c->cap_pixels));
   TRY(dalloc(&c->t_final, c->cap_pixels));
-  c->cap_scan_words = scan_scratch_words(std::max<int64_t>(std::max<int64_t>(c->cap_splats, c->cap_tiles),
-                                                            (int64_t)8192 * c->cap_frames));
-  TRY(dalloc(&c->scan_scratch, c->cap_scan_words));
+  TRY(dalloc(&c->scan_scratch, scan_scratch_words(c->cap_tiles)));   // the tile scan's block sums
   TRY(dalloc(&c->scan_scratch_splat, scan_scratch_words(c->cap_splats)));
   TRY(dalloc(&c->draw_scratch, c->cap_splats * kNF));
   TRY(dalloc(&c->loss_part, 2 * loss_partials(3 * c->cap_pixels) + 2));
@@ -695,7 +679,7 @@ int gbr_memory(gbr_ctx* c, int64_t* device_bytes) {
   if (!c || !device_bytes) return GBR_ERR_INVALID_ARG;
   WorkspaceCaps k{};
   k.frames = c->cap_frames; k.splats = c->cap_splats; k.pixels = c->cap_pixels; k.tiles = c->cap_tiles;
-  k.entries = c->cap_entries; k.bkt = c->cap_bkt; k.bkt_cells = c->cap_bkt_cells; k.scan_words = c->cap_scan_words;
+  k.entries = c->cap_entries; k.bkt = c->cap_bkt; k.bkt_cells = c->cap_bkt_cells;
   k.tbits = c->cap_tbits; k.seg = c->cap_seg;
   k.ci_pixels = c->ci_ones ? c->cap_pixels : 0;
   k.ci_splats = c->ci_ones ? c->cap_splats : 0;
@@ -722,11 +706,10 @@ int gbr_plan_bytes(const gbr_config* cfg, int32_t B, const int64_t* gauss_offset
     pix += (int64_t)widths[b] * heights[b];
   }
   if (gauss_offsets[B] > cfg->max_splats || pix > cfg->max_pixels || n_tiles > k.tiles) return GBR_ERR_CAPACITY;
-  int64_t bkt, cells, scan_words, tbits, seg;
-  pass_caps(B, mfs, n_tiles, mft, &bkt, &cells, &scan_words, &tbits, &seg);
+  int64_t bkt, cells, tbits, seg;
+  pass_caps(B, mfs, n_tiles, mft, &bkt, &cells, &tbits, &seg);
   // a pass grows a buffer only beyond its current capacity
   if (bkt > k.bkt || cells > k.bkt_cells) { k.bkt = bkt; k.bkt_cells = cells; }
-  k.scan_words = std::max(k.scan_words, scan_words);
   k.tbits = tbits;
   k.seg = seg;
   k.entries = std::max(k.entries, entries);
