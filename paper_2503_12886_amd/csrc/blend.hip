@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kBlendThreads) void blend_drive_kernel(DriveTable t
                     (int64_t)(blockIdx.x - t.block0[gi]) * kBlendThreads + threadIdx.x, g.raw);
 }
 
-int64_t blend_drive_blocks(int64_t N) { return div_up(N * kNF, kBlendThreads); }
+int64_t blend_drive_blocks(int64_t N) { return N / (kBlendThreads / kNF) + (N % (kBlendThreads / kNF) != 0); }
 
 // Models of one instance (slices in eights) share a launch, and those of fewer
 // slices join it while the slices they would read and multiply for nothing cost
@@ -398,12 +398,13 @@ __global__ __launch_bounds__(kRedCols * kRedRows) void reduce_partials_kernel(co
   if (r == 0 && i < BK) out[i] = accumulate ? out[i] + sm[0][c] : sm[0][c];
 }
 
+// Both counts are the entry points' limits on a shape and exceed what the launch
+// writes, a partial per workgroup, at most kDwBlocks of them.
 int64_t blend_bwd_partials(int B, int K, int64_t N) {
   const int64_t waves = (int64_t)div_up(N * kNF, 4 * kDwSpan) * 4;
   return waves * (int64_t)B * K;
 }
 
-// (an upper bound: the launch writes one partial per workgroup, at most kDwBlocks of them)
 int64_t blend_bwd_partials_used(int B, int K, int64_t N) {
   if (K == 0) return 0;
   const int64_t blocks = (int64_t)div_up(N * kNF, 4 * kDwSpan);

@@ -20,7 +20,6 @@ constexpr int kSlots = 5;          // pinned frame-table slots; the last one is 
 constexpr int kCaptureSlot = kSlots - 1;
 constexpr int kMaxK = 63;
 constexpr int kMaxFramesHard = 4096;
-constexpr int64_t kMaxBitmapWords = 32768;   // 128 KB bitmap row per tile: frames of up to 1,048,576 Gaussians
 
 // A failed HIP call is reported once: its error is also taken out of HIP's
 // last-error state, which the launch checks read, so that it does not

@@ -100,7 +100,7 @@ struct PassArgs {
   int32_t nblk;             // workgroups of kBucketBlock splats per frame in the bucket passes
   int32_t by_xcd;           // the depth and binning passes keep a frame's workgroups on one XCD (frame_block)
   int32_t bitmap_words;     // words per tile bitmap row (largest frame's splats / 32, rounded up to 16)
-  int32_t seg_words;        // words per row segment (8 or 16); a segment's set bits are counted once
+  int32_t seg_words;        // words per row segment (8, 16 or 32); a segment's set bits are counted once
   int32_t seg_stride;       // segments per row = bitmap_words / seg_words
   uint32_t* blk_mm;         // [2 per projection workgroup] min, max binary32 depth bits of its valid splats;
                             // frame b's workgroup j at gauss_base / 256 + b + j (frames never share one);
@@ -283,7 +283,7 @@ void launch_blend_bwd(const float* draw, const float* bases, const float* weight
                       float* dbases, float* dweights, float* partials, int64_t n_partials, int accumulate,
                       hipStream_t s);
 int64_t blend_bwd_partials(int B, int K, int64_t N);
-// an upper bound of the floats of partials launch_blend_bwd writes and reads for this shape
+// the limit of gbr_blend_backward_noalloc: no fewer floats than launch_blend_bwd writes for this shape
 int64_t blend_bwd_partials_used(int B, int K, int64_t N);
 // The grid of `per` workgroups a frame (frame_block).
 inline dim3 frame_grid(const PassArgs& a, int per) {
@@ -309,14 +309,19 @@ int64_t scan_scratch_words(int64_t n);
 // host_frames: null when the frame table is in device memory, else the host's
 // (at most kArgFrames frames), which the projection takes as an argument and
 // stores: the copy and its event before every eager pass cost a frame of 50k
-// Gaussians 6 us of 164, five of 30k (render and backward) 4 of 263.  More frames
-// would not fit a kernel's arguments beside the rest.
+// Gaussians 6 us of 164, five of 30k (render and backward) 4 of 263.  16 frames take
+// 2 of the 4 KB that a kernel's arguments may; more keep the copy, a smaller
+// part of their longer passes.
 constexpr int kArgFrames = 16;
 bool launch_preprocess(const PassArgs& a, const FrameDev* host_frames, const float* raw, int64_t max_frame_splats,
                        hipStream_t s);
 // Words per bitmap row segment for frames of up to max_frame_tiles tiles
-// (the workgroup that builds a segment of every row of a frame holds them in LDS).
-constexpr int kMaxRowSegs = 1024;   // segments per bitmap row at most (the compositing lists them in LDS)
+// (the workgroup that builds a segment of every row of a frame holds them in LDS):
+// 8 or 16, and 32 where a row would have more than kMaxRowSegs segments.  The
+// compositing reads a row's words 64 at a time, a whole number of segments.
+constexpr int64_t kMaxBitmapWords = 32768;   // 128 KB bitmap row per tile: frames of up to 1,048,576 Gaussians
+constexpr int kMaxRowSegs = 1024;            // segments per bitmap row at most
+static_assert(kMaxBitmapWords / kMaxRowSegs <= 64, "a segment fits a wave's read of 64 words");
 int bitmap_seg_words(int max_frame_tiles, int64_t row_words);
 void launch_bitmap_rows(const PassArgs& a, int64_t max_frame_splats, int max_frame_tiles, hipStream_t s);
 void launch_tile_lists(const PassArgs& a, hipStream_t s);

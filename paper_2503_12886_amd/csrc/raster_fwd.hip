@@ -309,6 +309,7 @@ struct ArgFrames {
     for (int i = threadIdx.x; i < a.B * (int)(sizeof(FrameDev) / 4); i += 256) dst[i] = src[i];
   }
 };
+static_assert(sizeof(PassArgs) + sizeof(ArgFrames) + sizeof(void*) <= 4096, "a kernel's arguments take 4 KB");
 
 template <typename Frames>
 __global__ __launch_bounds__(256) void preprocess_kernel(PassArgs a, Frames frames, const float* __restrict__ raw) {

@@ -33,3 +33,17 @@ def test_mixed(slices):
     for i, ((_, _, _, psi, raw), (p, r)) in enumerate(zip(groups, refs)):
         assert np.array_equal(host(psi), p) and np.array_equal(host(raw), r, equal_nan=True), (i, slices[i])
     ctx.close()
+
+
+@pytest.mark.parametrize("N", [1 << 36, (1 << 37) + 1, 1 << 40, (1 << 62) + 5])
+def test_sizes_beyond_a_grid_are_refused(N):
+    """More workgroups than a grid has: an error before anything is launched."""
+    import torch
+    ctx = make_ctx(max_frames=2)
+    t = torch.zeros(1 << 17, device="cuda")
+    p = t.data_ptr()
+    g = (gbr.gbr_drive_group * 2)(gbr.gbr_drive_group(p, p, p, p, p, 5, 1, 2), gbr.gbr_drive_group(p, p, p, p, p, N, 1, 2))
+    with pytest.raises(gbr.GbrError) as e:
+        gbr.gbr_drive(ctx, g, 4, 8)
+    assert e.value.code == -1
+    ctx.close()
