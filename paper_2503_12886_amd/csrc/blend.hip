@@ -439,8 +439,11 @@ void launch_blend_bwd(const float* draw, const float* bases, const float* weight
                       hipStream_t s) {
   if (N == 0 || B == 0) return;
   const dim3 g1(div_up(N * kNF, kBlendThreads));
+  // (past 40 slices one of 64, as for the update below: at 100k Gaussians and 8
+  // frames 43 slices 80 us so and 87 in an instance of 48, 55 slices 92 and 108
+  // in one of 56; 39 slices 77 and 72 in one of 40, 31 slices 60 and 53)
   if (dbases)
-    with_slices(K, [&](auto km) {
+    with_slices(K < 40 ? K : kBlendW64Stride - 1, [&](auto km) {
       hipLaunchKernelGGL(blend_dbases_kernel<km()>, g1, dim3(kBlendThreads), 0, s, draw, weights, B, K, N, dbases,
                          accumulate);
     });
