@@ -265,14 +265,13 @@ void launch_blend_adam(const float* draw, const float* weights, int B, int K, in
 // of the 4 components feeds one 16x16x4 product per 16 frames and 16 slices,
 // contracted over the 4 quarters.  The pad features (14, 15) are skipped.
 // The workgroup's four waves are added in LDS and it writes one [B][K]
-// partial.  At most kDwBlocks workgroups run, each wave over several spans
+// partial.  Of larger inputs kDwBlocks workgroups run, each wave over several spans
 // whose sums are added in span order, and the kernel is instantiated per 16
 // frames and 16 slices: bound by reading draw and the bases once.  64 frames
 // of 100k Gaussians x 20: 172 + 62 (reduction) -> 150 + 5 us, where a partial per
 // wave of 256 elements (32 MB, re-read at a stride of a partial) and products
-// of 64 x 64 for 64 x 20 had cost as much again as the reading.  (The line for
-// several spans: with twice the workgroups it takes 158 + 8, with as many
-// spans for every wave 172.)
+// of 64 x 64 for 64 x 20 had cost as much again as the reading.  (With twice the
+// workgroups it takes 158 + 8, with as many spans for every wave 172.)
 constexpr int kDwSpan = 256;
 constexpr int kDwBlocks = 1024;
 
@@ -448,7 +447,12 @@ void launch_blend_bwd(const float* draw, const float* bases, const float* weight
                          accumulate);
     });
   if (K == 0) return;
-  const int all = div_up(N * kNF, 4 * kDwSpan), blocks = std::min(all, kDwBlocks);
+  // (one or two products a block: a few more workgroups than kDwBlocks still
+  // finish sooner with a span each than some of their waves with two: 16 frames
+  // of 80k x 31 44 -> 40 us, 66k 40 -> 37; with more products, 32 frames of 80k x
+  // 20 67 -> 72, 64 of 97k x 8 102 -> 112)
+  const int line = B <= 16 && K <= 32 ? kDwBlocks * 3 / 2 : kDwBlocks;
+  const int all = div_up(N * kNF, 4 * kDwSpan), blocks = all > line ? kDwBlocks : all;
   if (all > blocks) launch_dweights<true>(blocks, draw, bases, B, K, N, partials, s);
   else launch_dweights<false>(blocks, draw, bases, B, K, N, partials, s);
   (void)n_partials;
