@@ -399,9 +399,10 @@ __device__ __forceinline__ float octets_transposed9(const float (&v)[9], int lan
 }
 #undef GBR_BANK_PAIR
 
+// (tiles of 8: 9.8 KB of LDS a wave leave room for 4 a SIMD)
 template <int T>
-__global__ __launch_bounds__(TileShapeB<T>::NT, 5) void composite_bwd_kernel(PassArgs a,
-                                                                             const float* __restrict__ dimages) {
+__global__ __launch_bounds__(TileShapeB<T>::NT, T == 8 ? 4 : 5) void composite_bwd_kernel(
+    PassArgs a, const float* __restrict__ dimages) {
   using S = TileShapeB<T>;
   static_assert(S::PX == 1 && S::QW == 8, "a pixel per lane, quadrants of 8 x 8");
   constexpr int NW = S::NW;
