@@ -632,7 +632,8 @@ void launch_composite_bwd(const PassArgs& a, const float* dimages, const float* 
 // one launch: the second launch's latencies cost more than it saves.
 // Measured, one launch against two (us): 100k splats 18 / 22, 150k 15 / 21,
 // 500k 47 / 44, 600k (half of them listed) 89 / 80, 800k 76 / 64, 6.4M
-// 361 / 287.
+// 361 / 287.  A gradient written over the Gaussians themselves takes one launch:
+// two would overwrite them with the sums before the adjoint reads them.
 constexpr int64_t kTwoPassSplats = 500000;
 
 // Flag bytes (0 or 1) of 4 entries -> 4 bits.
@@ -1023,7 +1024,7 @@ void launch_color_init_apply(const float* draw_i, const float* draw_1, int B, in
 
 void launch_gather_bwd(const PassArgs& a, const float* raw, float* draw, int64_t max_frame_splats, hipStream_t s) {
   if (a.n_splats == 0 || max_frame_splats == 0) return;
-  if (a.n_splats < kTwoPassSplats) {
+  if (a.n_splats < kTwoPassSplats || draw == raw) {
     hipLaunchKernelGGL(gather_adjoint_kernel, dim3(div_up(max_frame_splats, kAdjThreads), a.B), dim3(kAdjThreads), 0, s,
                        a, raw, draw);
     return;
