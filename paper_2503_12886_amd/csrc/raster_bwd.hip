@@ -332,7 +332,9 @@ __global__ __launch_bounds__(TileShapeB<32>::NT) void composite_bwd32_kernel(Pas
 // frames of 100k 1285 -> 1080, five of 333 x 500 166 -> 117, one of 128 x 128
 // 88 -> 56.  With alpha / (1 - alpha) in place of 1 / (1 - alpha), the clamp
 // in the power, and the rows' reads contiguous (below): 304 -> 294, 404 -> 391,
-// 1090 -> 1065, 118 -> 114, 56 -> 54.  Bound by instruction issue: 140M vector
+// 1090 -> 1065, 118 -> 114, 56 -> 54.  With the moments about the mean instead of
+// the quadrant's centre, and a t of 0 whatever the state: 292 -> 301, 388 -> 408,
+// 1054 -> 1080, 113 -> 119, 54 -> 57.  Bound by instruction issue: 148M vector
 // operations (204M at first), 80 % of the slots, 5 waves a SIMD by LDS.
 // A row of 64 pixels in LDS: the halves of the quadrant's rows (4 pixels, 16
 // bytes) in order of (half, row), so that the 8 lanes of an entry read 128
