@@ -160,7 +160,7 @@ int gbr_render_backward(gbr_ctx* ctx, const float* dimages, float* draw, void* s
 
 /* Adjoint of gbr_blend.  draw [B][N][16] -> dbases [(K+1)][N][16] (pads
    written 0) and dweights [B][K] (the contraction over N*16 runs on the
-   matrix cores with per-wave partials summed in a fixed order);
+   matrix cores with per-workgroup partials summed in a fixed order);
    accumulate != 0 adds into the outputs.  dbases may be NULL: then only
    dweights is formed (for gbr_blend_adam_step, which forms dbases itself).
    1 <= B <= 64, 0 <= K <= 63, B * N within the context's max_splats
@@ -173,9 +173,9 @@ int gbr_blend_backward(gbr_ctx* ctx, const float* draw, const float* bases, cons
    hipMalloc): no context, and nothing is allocated or freed.  The dweights
    partials go to a fixed 4 MiB device array of the library (one per device,
    its address looked up on the first call on that device and kept until the
-   process ends), so a shape whose partials exceed 2^20 floats --
-   ceil(N * 16 / 1024) * B * K, times 4 when B > 16 or K > 32 -- returns
-   GBR_ERR_CAPACITY (N = 50,000, B = 16, K = 20 needs 250,240).  Arguments,
+   process ends), so a shape for which ceil(N * 16 / 1024) * B * K, times 4
+   when B > 16 or K > 32 (no fewer floats than its partials take), exceeds 2^20
+   returns GBR_ERR_CAPACITY (N = 50,000, B = 16, K = 20: 250,240).  Arguments,
    layouts, limits (1 <= B <= 64, 0 <= K <= 63) and results as
    gbr_blend_backward, bit for bit.  Call it with the stream's device
    current.  Every call on a device shares that device's array: calls that
